@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "ls.h"
+#include "ls_class.h"
 #include "ls_cluster.h"
 #include "ls_internal.h"
 
@@ -53,6 +54,11 @@ size_t emis_offset_bytes(int32_t N, int32_t L) {
 size_t prior_stats_offset_bytes(int32_t N, int32_t L) {
     return emis_offset_bytes(N, L) + (size_t)L * (2 * sizeof(double) + 2 * sizeof(float)) +
            (size_t)(L + 1) * sizeof(double);
+}
+
+// Byte offset of the class section (ls_class.h), after everything else.
+size_t class_offset_bytes(int32_t N, int32_t L) {
+    return (prior_stats_offset_bytes(N, L) + (size_t)N * 2 * sizeof(double) + 255) / 256 * 256;
 }
 
 uint64_t fnv1a(uint64_t h, const void *data, size_t n) {
@@ -174,6 +180,102 @@ bool choose_shape(int32_t N, int prec, Shape *out, bool grad = false, bool prior
     return false;
 }
 
+// ---- class sweeps -------------------------------------------------------------
+// ls_model.reserved: 0 (no classes) or log2 of the block length + 256 times
+// the class words of a row.
+int class_lb(const ls_model *m) { return m->reserved & 255; }
+int class_words(const ls_model *m) { return (m->reserved >> 8) & 255; }
+
+// Donor words per wave and waves of the class sweep for kw class words: as
+// few waves as place N (one wave steps the classes, the others wait for it),
+// eight at most.
+bool class_shape(int32_t N, int prec, int kw, int *nslot, int *nwaves) {
+    const int vps = vgpr_per_slot(prec), words = (N + 63) / 64;
+    for (int nw = 1; nw <= 8; ++nw) {
+#define LS_MATCH(n)                                                            \
+    if (nw * n >= words && lsk::csweep_exists(n, kw, vps) && !(vps == 2 && n > 80)) { \
+        *nslot = n;                                                            \
+        *nwaves = nw;                                                          \
+        return true;                                                           \
+    }
+        LS_MENU_CSLOT_A(LS_MATCH)
+        LS_MENU_CSLOT_B(LS_MATCH)
+        LS_MENU_CSLOT_C(LS_MATCH)
+        LS_MENU_CSLOT_D(LS_MATCH)
+        LS_MENU_CSLOT_E(LS_MATCH)
+#undef LS_MATCH
+    }
+    return false;
+}
+
+// Vector instructions of one recipient step: the class sweep's (5 per class
+// word and about 30 around them, and at each block boundary about 10 per
+// donor word, its LDS accesses included) and the plain sweep's (3 per slot
+// and 34 per wave).
+double class_step_cost(int32_t N, int lb, int kw) {
+    return 5.0 * kw + 30.0 + 10.0 * ((N + 63) / 64) / (double)(1 << lb);
+}
+double plain_step_cost(int32_t N) {
+    Shape sh;
+    if (!choose_shape(N, LS_FP32, &sh)) return 0.0;
+    return sh.nwaves * (3.0 * sh.nslot + 34.0);
+}
+
+// Block length and class words for the largest class counts `most` of blocks
+// of 16, 32 and 64 variants; 0 if the plain sweep is predicted to be as good.
+int32_t choose_classes(int32_t N, const int32_t most[3]) {
+    double best = 0.8 * plain_step_cost(N);
+    int32_t pick = 0;
+    for (int b = 0; b < 3; ++b) {
+        if (most[b] > lsk::class_cap(N)) continue;
+        int kw = 0, ns = 0, nw = 0;
+        const int need = (most[b] + 63) / 64;
+#define LS_MATCH(v) \
+    if (kw == 0 && v >= need) kw = v;
+        LS_MENU_CLASS(LS_MATCH)
+#undef LS_MATCH
+        if (kw == 0 || 64 * kw > lsk::class_cap(N) || !class_shape(N, LS_FP32, kw, &ns, &nw)) continue;
+        const double c = class_step_cost(N, 4 + b, kw);
+        if (c < best) {
+            best = c;
+            pick = (4 + b) | (kw << 8);
+        }
+    }
+    return pick;
+}
+
+// Moves of fewer variants than this stay with the plain sweep, whose tables
+// resume to the same bits wherever a move is cut (the class sweep's agree to
+// rounding); a block boundary also costs as much as several plain steps.
+constexpr int kClassMinMove = 64;
+
+bool class_route(const ls_model *m, int prec, int variants) {
+    if (class_lb(m) == 0 || m->prior || variants < kClassMinMove) return false;
+    if (prec != LS_FP32 && prec != LS_FP64) return false;
+    int ns = 0, nw = 0;
+    if (!class_shape(m->N, prec, class_words(m), &ns, &nw)) return false;
+    return std::getenv("LS_FORCE_SHAPE") == nullptr;  // a forced shape is a plain sweep's
+}
+
+void class_ptrs(const ls_model *m, int prec, lsk::ClassPtrs &c) {
+    const lsk::ClassLayout lay = lsk::class_layout(m->N, m->L);
+    const char *base = reinterpret_cast<const char *>(m->Hr) + class_offset_bytes(m->N, m->L);
+    c.ids = reinterpret_cast<const uint32_t *>(base + lay.off_ids);
+    c.keys = reinterpret_cast<const uint64_t *>(base + lay.off_keys);
+    c.cnt = reinterpret_cast<const float *>(base + lay.off_cnt);
+    c.rows = reinterpret_cast<const uint64_t *>(base + lay.off_rows);
+    c.lr = reinterpret_cast<const double *>(base + lay.off_lr);
+    c.g = base + (prec == LS_FP64 ? lay.off_g64 : lay.off_g32);
+    const char *emis = reinterpret_cast<const char *>(m->Hr) + emis_offset_bytes(m->N, m->L);
+    const size_t L = (size_t)m->L;
+    c.r = prec == LS_FP64 ? base + lay.off_r64 : emis + 2 * L * sizeof(double);
+    c.lb = class_lb(m);
+    c.kw = class_words(m);
+    class_shape(m->N, prec, c.kw, &c.nslot, &c.nwaves);
+    c.unit = lsk::sweep_emissions(m->mu).unit;
+    c.mu_vec = m->mu_vec;
+}
+
 ls_status check_model(const ls_model *m) {
     if (!m || !m->Hr || m->hash == 0 || m->N < 2 || m->L < 1) return LS_ERR_ARG;
     return LS_OK;
@@ -248,6 +350,13 @@ void emission_tables(const ls_model *m, int prec, SweepPtrs &p) {
     }
 }
 
+// The prefix sums of the emission divisors' logs (vector mu).
+const double *log_unit_prefix(const ls_model *m) {
+    SweepPtrs p;
+    emission_tables(m, LS_FP32, p);
+    return p.lu_prefix;
+}
+
 hipError_t launch_sweep(int prec, int dir, const SweepPtrs &p, const SweepArgs &a, Shape sh,
                         hipStream_t st) {
     if (prec == LS_FP64)
@@ -283,7 +392,7 @@ int32_t sweep_chunk() {
 }
 
 hipError_t run_chunks(int prec, int dir, const SweepPtrs &p, const SweepArgs &a, Shape sh,
-                      hipStream_t st) {
+                      hipStream_t st, const lsk::ClassPtrs *cls = nullptr) {
     SweepArgs c = a;
     int32_t l0 = a.l0;
     int next = 0;  // next target, in travel order
@@ -291,8 +400,7 @@ hipError_t run_chunks(int prec, int dir, const SweepPtrs &p, const SweepArgs &a,
     for (;;) {
         int32_t tc;
         if (dir == 0) {
-            const int32_t from = l0 < 0 ? 0 : l0;
-            tc = std::min(a.t, from + chunk);
+            tc = lsk::forward_chunk_end(l0, a.t, chunk, cls ? cls->lb : 0);
         } else {
             const int32_t top = l0 < 0 ? a.L - 1 : l0;
             tc = std::max(a.t, top - chunk);
@@ -308,7 +416,8 @@ hipError_t run_chunks(int prec, int dir, const SweepPtrs &p, const SweepArgs &a,
         c.nt = n;
         c.l0 = l0;
         c.t = tc;
-        const hipError_t e = launch_sweep(prec, dir, p, c, sh, st);
+        const hipError_t e = cls ? lsk::launch_csweep(prec, p, *cls, c, st)
+                                 : launch_sweep(prec, dir, p, c, sh, st);
         if (e != hipSuccess || tc == a.t) return e;
         l0 = tc;
     }
@@ -319,11 +428,11 @@ hipError_t run_chunks(int prec, int dir, const SweepPtrs &p, const SweepArgs &a,
 // other's partly filled last round of workgroups, measured slower: the
 // concurrent launches cost more than the tail they fill.)
 hipError_t launch_sweep_chunked(int prec, int dir, const SweepPtrs &p, const SweepArgs &a,
-                                Shape sh, hipStream_t st) {
+                                Shape sh, hipStream_t st, const lsk::ClassPtrs *cls = nullptr) {
     SweepArgs b = a;
     b.r0 = 0;
     b.nblk = a.R;
-    return run_chunks(prec, dir, p, b, sh, st);
+    return run_chunks(prec, dir, p, b, sh, st, cls);
 }
 
 ls_status check_table(const ls_table *t, const ls_model *m, int dir) {
@@ -349,6 +458,7 @@ extern "C" {
 
 size_t ls_model_workspace_bytes(int32_t N, int32_t L) {
     if (N < 2 || L < 1) return 0;
+    if (lsk::class_section(N, L)) return class_offset_bytes(N, L) + lsk::class_layout(N, L).total;
     return prior_stats_offset_bytes(N, L) + (size_t)N * 2 * sizeof(double);
 }
 
@@ -358,7 +468,8 @@ ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *str
     if (m->stride_words < (m->N + 31) / 32 || (m->stride_words & 1)) return LS_ERR_ARG;
     if (!(m->mu >= 0.0 && m->mu <= 1.0)) return LS_ERR_ARG;
     if (m->L > 1 && !m->rho) return LS_ERR_ARG;
-    const size_t need = ls_model_workspace_bytes(m->N, m->L);
+    // a workspace without room for the class section runs the plain sweeps
+    const size_t need = prior_stats_offset_bytes(m->N, m->L) + (size_t)m->N * 2 * sizeof(double);
     if (!workspace || ws_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255))
         return LS_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
@@ -433,11 +544,41 @@ ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *str
             reinterpret_cast<double *>(eb + 2 * L * (sizeof(double) + sizeof(float))), st);
         if (e != hipSuccess) return LS_ERR_DEVICE;
     }
+    // haplotype classes: the class sweep keeps its values in range with
+    // powers of two taken out once a step, which covers these parameters
+    // (a jump factor of at most 10 and an emission ratio of at least 2^-30)
+    int32_t classes = 0;
+    bool in_range = lsk::class_section(m->N, m->L) && ws_bytes >= ls_model_workspace_bytes(m->N, m->L) &&
+                    !m->prior;
+    auto mu_fits = [](double mu) { return mu <= 0.5 && mu >= 0x1p-30; };
+    if (in_range && !m->mu_vec) in_range = mu_fits(m->mu);
+    for (size_t k = 0; in_range && k < muv.size(); ++k) in_range = mu_fits(muv[k]);
+    for (size_t k = 0; in_range && k < rho.size(); ++k) in_range = rho[k] <= 0.9;
+    if (in_range) {
+        char *section = static_cast<char *>(workspace) + class_offset_bytes(m->N, m->L);
+        const lsk::ClassLayout lay = lsk::class_layout(m->N, m->L);
+        int32_t *most = reinterpret_cast<int32_t *>(section + lay.off_max);
+        e = lsk::launch_fill_u32(reinterpret_cast<uint32_t *>(most), 0u, 4, st);
+        for (int b = 0; b < 3 && e == hipSuccess; ++b)
+            e = lsk::launch_class_count(Hr, hs, m->N, m->L, 4 + b, lsk::class_cap(m->N), most + b, st);
+        int32_t host_most[4];
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(host_most, most, sizeof host_most, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return LS_ERR_DEVICE;
+        classes = choose_classes(m->N, host_most);
+        if (classes) {
+            e = lsk::launch_class_build(Hr, hs, m->N, m->L, classes & 255, classes >> 8, section, lay, st);
+            if (e == hipSuccess)
+                e = lsk::launch_class_tables(m->rho, m->mu_vec, m->N, m->L, section, lay, st);
+            if (e != hipSuccess) return LS_ERR_DEVICE;
+        }
+    }
     m->hash = h;
     m->Hr = Hr;
     m->hr_stride = hs;
     m->nf = m->N / 64;
-    m->reserved = 0;
+    m->reserved = classes;
     return LS_OK;
 }
 
@@ -548,7 +689,10 @@ ls_status forward_impl(ls_table *fwd, const ls_model *m, int32_t t, const int32_
     p.status = fwd->status;
     p.snap = want_out ? stage : fwd->state;
     hipStream_t st = as_stream(stream);
-    hipError_t e = launch_sweep_chunked(fwd->prec, 0, p, a, sh, st);
+    lsk::ClassPtrs cls;
+    const bool by_class = class_route(m, fwd->prec, t - std::max(fwd->l, 0));
+    if (by_class) class_ptrs(m, fwd->prec, cls), p.lu_prefix = log_unit_prefix(m);
+    hipError_t e = launch_sweep_chunked(fwd->prec, 0, p, a, sh, st, by_class ? &cls : nullptr);
     if (e != hipSuccess) return LS_ERR_DEVICE;
     if (want_out) {
         e = lsk::launch_posterior_rows(stage, 0, bsnap, 0, fwd->recipients, fwd->R, T, ts, rs,
@@ -612,7 +756,11 @@ ls_status ls_backward(ls_table *bck, const ls_model *m, int32_t t, const int32_t
     p.log_scale = bck->log_scale;
     p.status = bck->status;
     p.snap = T > 0 ? bsnap : bck->state;
-    hipError_t e = launch_sweep_chunked(bck->prec, 1, p, a, sh, as_stream(stream));
+    lsk::ClassPtrs cls;
+    const bool by_class = class_route(m, bck->prec, top - t);
+    if (by_class) class_ptrs(m, bck->prec, cls), p.lu_prefix = log_unit_prefix(m);
+    hipError_t e = launch_sweep_chunked(bck->prec, 1, p, a, sh, as_stream(stream),
+                                        by_class ? &cls : nullptr);
     if (e != hipSuccess) return LS_ERR_DEVICE;
     bck->l = t;
     bck->model_hash = m->hash;
@@ -783,6 +931,11 @@ ls_status loglik_grad_impl(const ls_model *m, const int32_t *recipients, int32_t
         SweepPtrs e64;
         emission_tables(m, LS_FP64, e64);
         ga.em64 = static_cast<const double *>(e64.emis);
+    }
+    ga.by_class = class_route(m, prec, m->L - 1);
+    if (ga.by_class) {
+        class_ptrs(m, prec, ga.cls);
+        ga.class_lu_prefix = log_unit_prefix(m);
     }
     ga.chunk = sweep_chunk();
     if (!choose_shape(m->N, prec, &ga.fwd_shape, false, m->prior != nullptr))

@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "ls_class.h"
 #include "ls_grad_kernel.h"
 
 namespace lsk {
@@ -175,6 +176,10 @@ hipError_t launch_grad(const GradArgs &ga, int prec, Shape sh, double *loglik, d
             a.tgt_out[0] = tl[0];
             return prec == 0 ? launch_every_f64(p, a, sh, st) : launch_every_f32(p, a, sh, st);
         }
+        if (ga.by_class) {
+            p.lu_prefix = ga.class_lu_prefix;
+            return launch_csweep(prec, p, ga.cls, a, st);
+        }
         return prec == 0 ? launch_sweep_f64_fwd(p, a, ga.fwd_shape, st)
                          : launch_sweep_f32_fwd(p, a, ga.fwd_shape, st);
     };
@@ -193,7 +198,7 @@ hipError_t launch_grad(const GradArgs &ga, int prec, Shape sh, double *loglik, d
         std::vector<int32_t> tl(2 * kMaxTargets);
         int l0 = -1, knext = 0;
         while (l0 < ga.L - 1) {
-            int t = std::min(ga.L - 1, (l0 < 0 ? 0 : l0) + ga.chunk);
+            int t = forward_chunk_end(l0, ga.L - 1, ga.chunk, ga.by_class ? ga.cls.lb : 0);
             int nt = 0;
             for (; knext < ga.nseg && knext * ga.seg <= t && nt < kMaxTargets; ++knext, ++nt) {
                 tl[2 * nt] = knext * ga.seg;

@@ -271,6 +271,32 @@ struct GradLayout {
 size_t grad_workspace_bytes(int32_t N, int32_t L, int32_t R, int prec, bool muv,
                             GradLayout *lay);
 
+// What a class sweep reads besides the arguments of a plain sweep
+// (ls_class.h).
+struct ClassPtrs {
+    const uint32_t *ids;
+    const uint64_t *keys;
+    const float *cnt;
+    const uint64_t *rows;
+    const double *lr;
+    const void *g;         // [L+1] in the arithmetic type
+    const void *r;         // vector mu: emission of a mismatch [L]; FP32: the pairs [L][2]
+    int32_t lb, kw;        // log2 of the block length; words per class row
+    int32_t nslot, nwaves; // donor words per wave, waves per recipient
+    double unit;           // the emission divisor of a scalar mu, and
+    const double *mu_vec;  // the mutation probabilities of a vector mu
+};
+// Last variant of the forward launch that resumes from l0 on the way to t, at
+// most `chunk` variants on; with class blocks of 2^lb variants (lb > 0) it
+// ends with a block where it can, which saves a boundary pass.
+inline int32_t forward_chunk_end(int32_t l0, int32_t t, int32_t chunk, int lb) {
+    const int32_t from = l0 < 0 ? 0 : l0;
+    if (t - from <= chunk) return t;
+    const int32_t end = from + chunk;
+    const int32_t whole = lb ? (((end + 1) >> lb) << lb) - 1 : end;
+    return whole > from ? whole : end;
+}
+
 struct GradArgs {
     const uint64_t *Hr;
     const double *rho;
@@ -289,6 +315,9 @@ struct GradArgs {
     const double *em64;
     const double *lu_prefix;
     const double *prior;  // prior copying matrix ([N][N], row i = column i), or null
+    bool by_class;        // the checkpointing forward runs as a class sweep
+    ClassPtrs cls;
+    const double *class_lu_prefix;
     char *ws;
     GradLayout lay;
 };

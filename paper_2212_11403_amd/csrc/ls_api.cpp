@@ -140,6 +140,25 @@ double shape_cost(int32_t N, int prec, int ns, int nw, int wps = 0, bool sweep =
     return (double)nw * ops * std::max(1.0, hide / occ) * std::pow(imb, ex);
 }
 
+// Panels of at most 2,048 haplotypes (the gradient's passes and sweeps with a
+// prior matrix: 512): one wave per recipient, with the fewest slots that hold
+// them. Their groups never fill the SIMDs, so a step costs its latency, which
+// the exchange between waves doubles (ls_sweep.h). Measured in us per variant,
+// forward / backward, all recipients, against the best group of several waves:
+// FP32 N = 300 0.30/0.30 (0.38/0.37), 800 0.53/0.52 (0.50/0.45), 2,000
+// 0.70/0.74 (0.80/0.74); FP64 N = 200 0.31/0.27 (0.43/0.41), 500 0.36/0.32
+// (0.50/0.48), 1,500 0.84/0.76 (0.98/0.89).
+bool choose_one_wave(int32_t N, int prec, Shape *out, bool grad, bool prior) {
+    const int words = (N + 63) / 64;
+    if (words > (grad || prior ? 8 : lsk::kOneWaveSlots)) return false;
+    for (int ns : menu(prec, grad))
+        if (ns >= words && shape_fits(N, prec, ns, 1, prior)) {
+            *out = Shape{ns, 1};
+            return true;
+        }
+    return false;
+}
+
 // Cheapest shape by shape_cost; among shapes within 1% of the cheapest, the
 // one with the fewest waves (then the fewest slots). Depends on N and the
 // precision only, so a given problem always runs with the same summation
@@ -155,6 +174,9 @@ bool choose_shape(int32_t N, int prec, Shape *out, bool grad = false, bool prior
         }
     }
     const int vps = vgpr_per_slot(prec);
+    // small panels: one wave with the fewest slots that hold N (the measured
+    // best, see choose_one_wave)
+    if (choose_one_wave(N, prec, out, grad, prior)) return true;
     for (int pass = grad ? 0 : 1; pass < 2; ++pass) {
         auto ok = [&](int ns, int nw) {
             return shape_fits(N, prec, ns, nw, prior) &&

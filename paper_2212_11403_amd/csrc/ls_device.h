@@ -142,10 +142,10 @@ __device__ __forceinline__ void wave_sum4(const double (&x)[4], double (&w)[4]) 
 // then reads entry k and the first ceil-pow2(MAXW) lanes are added with the
 // same DPP butterflies on every wave, so the result is identical across waves
 // and runs. One barrier per call; `parity` alternates so consecutive calls
-// never reuse a buffer another wave may still be reading. A single-wave group
-// takes the same path (its other entries are 0): a branch on the wave count,
-// like a loop over it, makes the register allocator spill the resident vector
-// inside the variant loop.
+// never reuse a buffer another wave may still be reading. A branch on the wave
+// count, like a loop over it, makes the register allocator spill the resident
+// vector inside the variant loop; kernels of single-wave groups are their own
+// instantiations (MAXW = 1), whose sum is the wave's (the others would add 0).
 constexpr int kRedStride = 64;
 
 // Sum of lanes 0..MAXW-1 (MAXW <= 16), returned as a scalar. The quad

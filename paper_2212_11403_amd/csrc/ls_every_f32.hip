@@ -12,27 +12,24 @@ static hipError_t launch_every_one(const SweepPtrs &p, const SweepArgs &a, int n
     if (nwaves < 1 || nwaves > max_waves_for(NSLOT, vps, p.prior != nullptr))
         return hipErrorInvalidValue;
     if (a.nblk < 1 || a.r0 < 0 || a.r0 + a.nblk > a.R) return hipErrorInvalidValue;
-    if (p.emis && p.prior)
-        hipLaunchKernelGGL((sweep_kernel<PT, NSLOT, 0, true, true, true>), dim3(a.nblk),
-                           dim3(64 * nwaves), 0, st, p.Hr, (const typename PT::T *)p.emis,
-                           p.lu_prefix, p.prior, p.rho, p.coef, p.recipients,
-                           (typename PT::ST *)p.state, p.log_scale, p.status,
-                           (typename PT::IO *)p.snap, a);
-    else if (p.prior)
-        hipLaunchKernelGGL((sweep_kernel<PT, NSLOT, 0, true, false, true>), dim3(a.nblk),
-                           dim3(64 * nwaves), 0, st, p.Hr, nullptr, nullptr, p.prior, p.rho,
-                           p.coef, p.recipients, (typename PT::ST *)p.state, p.log_scale,
-                           p.status, (typename PT::IO *)p.snap, a);
-    else if (p.emis)
-        hipLaunchKernelGGL((sweep_kernel<PT, NSLOT, 0, true, true>), dim3(a.nblk),
-                           dim3(64 * nwaves), 0, st, p.Hr, (const typename PT::T *)p.emis,
-                           p.lu_prefix, nullptr, p.rho, p.coef, p.recipients, (typename PT::ST *)p.state,
-                           p.log_scale, p.status, (typename PT::IO *)p.snap, a);
-    else
-        hipLaunchKernelGGL((sweep_kernel<PT, NSLOT, 0, true>), dim3(a.nblk), dim3(64 * nwaves), 0,
-                           st, p.Hr, nullptr, nullptr, nullptr, p.rho, p.coef, p.recipients,
-                           (typename PT::ST *)p.state, p.log_scale, p.status,
-                           (typename PT::IO *)p.snap, a);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(a.nblk), dim3(64 * nwaves), 0, st, p.Hr,
+                           (const PT::T *)p.emis, p.lu_prefix, p.prior, p.rho, p.coef, p.recipients,
+                           (PT::ST *)p.state, p.log_scale, p.status, (PT::IO *)p.snap, a);
+    };
+    auto pick = [&](auto one) {
+        constexpr bool ONE = decltype(one)::value;
+        if (p.prior && p.emis) go(&sweep_kernel<PT, NSLOT, 0, true, true, true, ONE>);
+        else if (p.prior) go(&sweep_kernel<PT, NSLOT, 0, true, false, true, ONE>);
+        else if (p.emis) go(&sweep_kernel<PT, NSLOT, 0, true, true, false, ONE>);
+        else go(&sweep_kernel<PT, NSLOT, 0, true, false, false, ONE>);
+    };
+    if constexpr (NSLOT <= kOneWaveSlotsGrad) {
+        if (nwaves == 1) pick(std::true_type{});
+        else pick(std::false_type{});
+    } else {
+        pick(std::false_type{});
+    }
     return hipGetLastError();
 }
 

@@ -64,8 +64,8 @@ __host__ __device__ constexpr int grad_kernel_waves(int nslot, int vgpr_per_slot
                           : 4);
 }
 
-template <class PT, int NSLOT, bool NARROW, bool MUV = false, bool PI = false>
-__global__ void __launch_bounds__(64 * grad_kernel_waves(NSLOT, PT::vgpr_per_slot, NARROW, PI))
+template <class PT, int NSLOT, bool NARROW, bool MUV = false, bool PI = false, bool ONE = false>
+__global__ void __launch_bounds__(ONE ? 64 : 64 * grad_kernel_waves(NSLOT, PT::vgpr_per_slot, NARROW, PI))
 grad_seg_kernel(const uint64_t *__restrict__ Hr, const double *__restrict__ rho,
                 const float *__restrict__ coef, const float *__restrict__ coefb,
                 const int32_t *__restrict__ recipients,
@@ -79,7 +79,7 @@ grad_seg_kernel(const uint64_t *__restrict__ Hr, const double *__restrict__ rho,
     using T = typename PT::T;
     constexpr int K = special_slots(NSLOT);
     constexpr int NR = NSLOT - K;
-    constexpr int MAXW = grad_kernel_waves(NSLOT, PT::vgpr_per_slot, NARROW, PI);
+    constexpr int MAXW = ONE ? 1 : grad_kernel_waves(NSLOT, PT::vgpr_per_slot, NARROW, PI);
     __shared__ T red[2 * kRedStride];
 
     const int nwaves = uniform(blockDim.x >> 6);
@@ -368,23 +368,24 @@ hipError_t launch_grad_seg(const GradArgs &ga, const GradSegArgs &sa, int nwaves
     const float *coefb = sizeof(T) == 4 ? ga.coef_bwd32 : nullptr;
     const T *emis = reinterpret_cast<const T *>(ga.emis);
     double *gmul = reinterpret_cast<double *>(ws + L.off_gmul);
-    if (ga.emis && ga.prior)
-        hipLaunchKernelGGL((grad_seg_kernel<PT, NSLOT, NARROW, true, true>), dim3(ga.R),
-                           dim3(64 * nwaves), 0, st, ga.Hr, ga.rho, coef, coefb, ga.recipients,
-                           alpha0, aseg, cval, ybuf, grow, gmu, emis, ga.em64, gmul, ga.prior, sa);
-    else if (ga.prior)
-        hipLaunchKernelGGL((grad_seg_kernel<PT, NSLOT, NARROW, false, true>), dim3(ga.R),
-                           dim3(64 * nwaves), 0, st, ga.Hr, ga.rho, coef, coefb, ga.recipients,
-                           alpha0, aseg, cval, ybuf, grow, gmu, nullptr, nullptr, nullptr,
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(ga.R), dim3(64 * nwaves), 0, st, ga.Hr, ga.rho, coef, coefb,
+                           ga.recipients, alpha0, aseg, cval, ybuf, grow, gmu, emis, ga.em64, gmul,
                            ga.prior, sa);
-    else if (ga.emis)
-        hipLaunchKernelGGL((grad_seg_kernel<PT, NSLOT, NARROW, true>), dim3(ga.R),
-                           dim3(64 * nwaves), 0, st, ga.Hr, ga.rho, coef, coefb, ga.recipients,
-                           alpha0, aseg, cval, ybuf, grow, gmu, emis, ga.em64, gmul, nullptr, sa);
-    else
-        hipLaunchKernelGGL((grad_seg_kernel<PT, NSLOT, NARROW>), dim3(ga.R), dim3(64 * nwaves), 0,
-                           st, ga.Hr, ga.rho, coef, coefb, ga.recipients, alpha0, aseg, cval, ybuf,
-                           grow, gmu, nullptr, nullptr, nullptr, nullptr, sa);
+    };
+    auto pick = [&](auto one) {
+        constexpr bool ONE = decltype(one)::value;
+        if (ga.emis && ga.prior) go(&grad_seg_kernel<PT, NSLOT, NARROW, true, true, ONE>);
+        else if (ga.prior) go(&grad_seg_kernel<PT, NSLOT, NARROW, false, true, ONE>);
+        else if (ga.emis) go(&grad_seg_kernel<PT, NSLOT, NARROW, true, false, ONE>);
+        else go(&grad_seg_kernel<PT, NSLOT, NARROW, false, false, ONE>);
+    };
+    if constexpr (NARROW && NSLOT <= kOneWaveSlotsGrad) {
+        if (nwaves == 1) pick(std::true_type{});
+        else pick(std::false_type{});
+    } else {
+        pick(std::false_type{});
+    }
     return hipGetLastError();
 }
 

@@ -146,6 +146,10 @@ __host__ __device__ constexpr int sweep_waves_per_simd(int nslot, int vgpr_per_s
     return w > 8 ? 8 : (w < 1 ? 1 : w);
 }
 
+// Single-wave groups have instantiations of their own up to this slot count.
+constexpr int kOneWaveSlots = 32;
+constexpr int kOneWaveSlotsGrad = 16;
+
 // Slot count whose sweep_waves_per_simd budget the sweep kernel is compiled
 // for. The keep-alpha mode (the gradient's recompute) holds more
 // registers: in FP32 about two per slot (measured).

@@ -91,8 +91,14 @@ __device__ __forceinline__ SpecSlot special_slot(int q, int NF, int N, int g, bo
 // b = kappa rho W' / ((N-1) S), whose entries stay below kappa (N-1) for
 // any prior; its log scale adds log(S / ((N-1) kappa)) per step, which keeps
 // the stored vector times exp(log scale) equal to kappa' beta^l G^l.
-template <class PT, int NSLOT, int DIR, bool EVERY = false, bool MUV = false, bool PI = false>
-__global__ void __launch_bounds__(64 * max_waves_for(NSLOT, sweep_slot_vgprs(PT::vgpr_per_slot, PI), PI))
+// ONE: single-wave groups. A narrow group's step is a chain of latencies, and
+// the exchange between waves (LDS write, barrier, read, four more additions)
+// is the longest link of it: us per variant at N = 300 FP32 0.50 (8 waves of
+// one slot) -> 0.30 (one of 8), N = 200 FP64 0.48 -> 0.31, N = 64 FP32 0.30 ->
+// 0.20.
+template <class PT, int NSLOT, int DIR, bool EVERY = false, bool MUV = false, bool PI = false,
+          bool ONE = false>
+__global__ void __launch_bounds__(ONE ? 64 : 64 * max_waves_for(NSLOT, sweep_slot_vgprs(PT::vgpr_per_slot, PI), PI))
 __attribute__((amdgpu_waves_per_eu(
     sweep_waves_per_simd(sweep_budget_slots(NSLOT, sweep_slot_vgprs(PT::vgpr_per_slot, PI), EVERY),
                          sweep_slot_vgprs(PT::vgpr_per_slot, PI)))))
@@ -111,7 +117,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     using IO = typename PT::IO;
     constexpr int K = special_slots(NSLOT);
     constexpr int NR = NSLOT - K;
-    constexpr int MAXW = max_waves_for(NSLOT, sweep_slot_vgprs(PT::vgpr_per_slot, PI), PI);
+    constexpr int MAXW = ONE ? 1 : max_waves_for(NSLOT, sweep_slot_vgprs(PT::vgpr_per_slot, PI), PI);
     // emission as a lane-masked multiply (every sweep whose emission pairs
     // have a member equal to 1: all but FP64 with a per-variant mu), except
     // the gradient's keep-alpha recompute, where the select form measured
@@ -294,6 +300,29 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     auto mask_of = [&](const uint64_t *row, int s) __attribute__((always_inline)) -> uint64_t {
         return (s < NR) ? row[reg_base + s] : row[spec_off[s - NR]];
     };
+    // Narrow single-wave groups read the row words one variant ahead, beside
+    // the coefficients (8 slots: 16 scalar registers). In a group of several
+    // waves the wait for the exchange through LDS waits for scalar loads too,
+    // so the loads gain nothing there and the copies cost 5 to 10%.
+    constexpr bool AHEAD = ONE && NSLOT <= 12;
+    struct Words {
+        uint64_t w[AHEAD ? NSLOT : 1];
+    };
+    auto words_at = [&](int l) __attribute__((always_inline)) -> Words {
+        Words x;
+        if constexpr (AHEAD) {
+            const uint64_t *row = Hr + (int64_t)l * a.hr_stride;
+#pragma unroll
+            for (int s = 0; s < NSLOT; ++s) x.w[s] = mask_of(row, s);
+        } else {
+            x.w[0] = 0;
+        }
+        return x;
+    };
+    auto step_mask = [&](const uint64_t *row, const Words &x, int s) __attribute__((always_inline)) -> uint64_t {
+        if constexpr (AHEAD) return x.w[s];
+        else return mask_of(row, s);
+    };
     // The emission as a lane-masked multiply (masked_scale4): one member of
     // the pair is exactly 1 (the pair divided by its larger member), so only
     // the donors taking the other value r are scaled. They are the lanes of
@@ -319,12 +348,11 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         // scalar register, which the EXEC arithmetic needs
         flip = uniform((int)(rb != on_match)) ? ~0ull : 0ull;
     };
-    auto xmul_all = [&](const uint64_t *row, uint64_t flip, T r) __attribute__((always_inline)) {
-        masked_scale_all<NSLOT>(
-            v, [&](int s) __attribute__((always_inline)) { return mask_of(row, s); }, flip, r);
+    auto xmul_all = [&](auto mask, uint64_t flip, T r) __attribute__((always_inline)) {
+        masked_scale_all<NSLOT>(v, mask, flip, r);
     };
     // v <- theta^l (.) (c v + b); returns this lane's partial sum
-    auto step = [&](int l, uint64_t sw_bits, T em, T ex, T c, T b_s)
+    auto step = [&](int l, uint64_t sw_bits, T em, T ex, T c, T b_s, const Words &wx)
                     __attribute__((always_inline)) -> T {
         const uint64_t *row = Hr + (int64_t)l * a.hr_stride;
         const T b = in_vgpr(b_s);
@@ -350,7 +378,8 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             // FP16 storage rounds what a table holds: the backward vector
             // kappa beta^l before its emission, the forward kappa alpha^l
             if constexpr (DIR == 1) quantise();
-            xmul_all(row, flip, r);
+            xmul_all([&](int s) __attribute__((always_inline)) { return step_mask(row, wx, s); },
+                     flip, r);
             if constexpr (DIR == 0) quantise();
 #pragma unroll
             for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc0, acc1);
@@ -361,7 +390,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         thetas(sw_bits, em, ex, ta, tb);
 #pragma unroll
         for (int s = 0; s < NSLOT; ++s) {
-            const T th = lane_bit(mask_of(row, s)) ? tb : ta;
+            const T th = lane_bit(step_mask(row, wx, s)) ? tb : ta;
             T bb;
             if constexpr (PI && DIR == 0) bb = b * pv[s];
             else bb = (s < NR) ? (s == 0 ? b * keep0 : b) : b * spec_keep[s - NR];
@@ -387,7 +416,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             T r;
             uint64_t flip;
             xmul_params(row[self_off], em, ex, r, flip);
-            xmul_all(row, flip, r);
+            xmul_all([&](int s) __attribute__((always_inline)) { return mask_of(row, s); }, flip, r);
 #pragma unroll
             for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc0, acc1);
             if constexpr (SNORM) part_w = aw0 + aw1;
@@ -481,22 +510,40 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     // at l = 0 gives c = 0, b = kappa / (N-1), i.e. alpha^0); backward
     // variant l uses rho_l. A decoding forward sweep has the emission
     // divisor in A and B (cnum, bmul), so its vector is kappa alpha^l.
-    auto coefs_at = [&](int l, T &A, T &B) __attribute__((always_inline)) {
+    // What is read ahead is the table pair (FP32) or rho (FP64), and A and B
+    // are formed from it when the step begins: formed at once, they would
+    // wait for the load.
+    struct Coef {
+        T x, y;
+    };
+    auto coef_read = [&](int l) __attribute__((always_inline)) -> Coef {
+        if constexpr (sizeof(T) == 4) return Coef{coef[2 * l], coef[2 * l + 1]};
+        else if constexpr (DIR == 0) return Coef{rho[l > 0 ? l - 1 : 0], (T)0};  // no branch: it costs registers
+        else return Coef{rho[l], (T)0};
+    };
+    // (held in vector registers: left to itself the compiler reads the kernel
+    // arguments again at every step and waits for them)
+    T cnum = (T)a.cnum, bmul = (T)a.bmul;
+    if constexpr (sizeof(T) == 8 && NSLOT <= 64) {
+        cnum = in_vgpr(cnum);
+        bmul = in_vgpr(bmul);
+    }
+    auto coef_form = [&](int l, const Coef &q, T &A, T &B) __attribute__((always_inline)) {
         if constexpr (sizeof(T) == 4) {
-            A = coef[2 * l];
-            B = coef[2 * l + 1];
+            A = q.x;
+            B = q.y;
         } else if constexpr (DIR == 0) {
-            // the load is unconditional: a branch here costs registers
-            const double r0 = rho[l > 0 ? l - 1 : 0];
-            const double rr = l > 0 ? r0 : 1.0;
+            const double rr = l > 0 ? q.x : 1.0;
             const double keep = l > 0 ? 1.0 : 0.0;
-            A = keep * (1.0 - rr) * a.cnum;
-            B = rr * a.bmul;
+            A = keep * (1.0 - rr) * cnum;
+            B = rr * bmul;
         } else {
-            const double rr = rho[l];
-            A = (1.0 - rr) * a.cnum;
-            B = rr * a.bmul;
+            A = (1.0 - q.x) * cnum;
+            B = q.x * bmul;
         }
+    };
+    auto coefs_at = [&](int l, T &A, T &B) __attribute__((always_inline)) {
+        coef_form(l, coef_read(l), A, B);
     };
     // c = A / S in the sweep precision. FP64 divides (correctly rounded).
     // FP32 refines the hardware reciprocal (about 1 ulp, and its error has a
@@ -571,19 +618,35 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             const rsrc_t rs_c =
                 make_rsrc(snap + a.c_off, (uint32_t)((a.t - a.l0) * a.R * (int)sizeof(IO)));
             const int c_voff = threadIdx.x == 0 ? r * (int)sizeof(IO) : 0x7ffffff0;
-            T A_nx, B_nx, em_nx, ex_nx;
-            coefs_at(l <= lmax ? l : lmax, A_nx, B_nx);
+            // byte offset of each lane and regular slot in a snapshot row: kept
+            // by narrow waves, formed again at every store by wide ones
+            int reg_voff[NR <= 12 ? (NR > 0 ? NR : 1) : 1];
+            if constexpr (NR <= 12) {
+#pragma unroll
+                for (int s = 0; s < NR; ++s) {
+                    int w = reg_base + s;
+                    if (w >= NF) w -= NF;
+                    reg_voff[s] = (w * 64 + lane) * (int)sizeof(IO);
+                }
+            }
+            T em_nx, ex_nx;
+            Coef q_nx = coef_read(l <= lmax ? l : lmax);
             emis_at(l <= lmax ? l : lmax, em_nx, ex_nx);
             uint64_t w_nx = self_word(l <= lmax ? l : lmax);
+            Words x_nx = words_at(l <= lmax ? l : lmax);
             for (; l <= a.t; ++l) {
-                const T A = A_nx, B = B_nx, em = em_nx, ex = ex_nx;
+                T A, B;
+                coef_form(l, q_nx, A, B);
+                const T em = em_nx, ex = ex_nx;
                 const uint64_t wb = w_nx;
+                const Words wx = x_nx;
                 const int ln = l < lmax ? l + 1 : lmax;
-                coefs_at(ln, A_nx, B_nx);
+                q_nx = coef_read(ln);
                 emis_at(ln, em_nx, ex_nx);
                 w_nx = self_word(ln);
+                x_nx = words_at(ln);
                 const T c = coef_c(A, S);
-                T part = step(l, wb, em, ex, c, B);
+                T part = step(l, wb, em, ex, c, B, wx);
                 buf_store((IO)c, rs_c, c_voff, (l - a.l0 - 1) * a.R * (int)sizeof(IO));
                 S = block_sum<MAXW>(part, red, parity, wave, nwaves);
                 account(S);
@@ -602,7 +665,10 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                     if (s < NR) {
                         int w = rb + s;
                         if (w >= NF) w -= NF;
-                        buf_store((IO)v[s], rs, voff, w * 64 * (int)sizeof(IO), kStreaming);
+                        if constexpr (NR <= 12)
+                            buf_store((IO)v[s], rs, reg_voff[s], 0, kStreaming);
+                        else
+                            buf_store((IO)v[s], rs, voff, w * 64 * (int)sizeof(IO), kStreaming);
                     } else {
                         buf_store((IO)v[s], rs, spec_byte[s - NR], 0, kStreaming);
                     }
@@ -613,17 +679,22 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             }
         } else for (;;) {
             const int lend = kt < a.nt ? a.tgt_l[kt] : a.t;
-            T A_nx, B_nx, em_nx, ex_nx;
-            coefs_at(l <= lmax ? l : lmax, A_nx, B_nx);
+            T em_nx, ex_nx;
+            Coef q_nx = coef_read(l <= lmax ? l : lmax);
             emis_at(l <= lmax ? l : lmax, em_nx, ex_nx);
             uint64_t w_nx = self_word(l <= lmax ? l : lmax);
+            Words x_nx = words_at(l <= lmax ? l : lmax);
             for (; l <= lend; ++l) {
-                const T A = A_nx, b = B_nx, em = em_nx, ex = ex_nx;
+                T A, b;
+                coef_form(l, q_nx, A, b);
+                const T em = em_nx, ex = ex_nx;
                 const uint64_t wb = w_nx;
+                const Words wx = x_nx;
                 const int ln = l < lmax ? l + 1 : lmax;
-                coefs_at(ln, A_nx, B_nx);
+                q_nx = coef_read(ln);
                 emis_at(ln, em_nx, ex_nx);
                 w_nx = self_word(ln);
+                x_nx = words_at(ln);
                 // c of this variant at the top of the step: its reciprocal
                 // chain then overlaps the scalar address work of the step,
                 // and the FP64 log-scale update sits after the reduction,
@@ -631,7 +702,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 // -> 18.0 ms per 2,048 variants with c formed after the
                 // reduction instead)
                 const T c = coef_c(A, S);
-                T part = step(l, wb, em, ex, c, b);
+                T part = step(l, wb, em, ex, c, b, wx);
                 S = block_sum<MAXW>(part, red, parity, wave, nwaves);
                 account(S);
             }
@@ -654,20 +725,25 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 const int lend = kt < a.nt ? a.tgt_l[kt] : a.t;
                 // the coefficients and the recipient's own word are read one
                 // variant ahead
-                T A_nx, B_nx, em_nx, ex_nx;
-                coefs_at(l, A_nx, B_nx);
+                T em_nx, ex_nx;
+                Coef q_nx = coef_read(l);
                 emis_at(l, em_nx, ex_nx);
                 uint64_t w_nx = self_word(l);
+                Words x_nx = words_at(l);
                 for (; l > lend; --l) {
-                    const T A = A_nx, B = B_nx, em = em_nx, ex = ex_nx;
+                    T A, B;
+                    coef_form(l, q_nx, A, B);
+                    const T em = em_nx, ex = ex_nx;
                     const uint64_t wb = w_nx;
+                    const Words wx = x_nx;
                     const int ln = l > 0 ? l - 1 : 0;
-                    coefs_at(ln, A_nx, B_nx);
+                    q_nx = coef_read(ln);
                     emis_at(ln, em_nx, ex_nx);
                     w_nx = self_word(ln);
+                    x_nx = words_at(ln);
                     const T c = coef_c(A, S);
                     const T b = SNORM ? coef_c(B * Wsum, S) : B;
-                    part = step(l, wb, em, ex, c, b);
+                    part = step(l, wb, em, ex, c, b, wx);
                     S = reduce(part);
                     account(S);
                 }

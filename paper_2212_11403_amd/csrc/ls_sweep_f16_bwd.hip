@@ -10,25 +10,24 @@ static hipError_t launch_one(const SweepPtrs &p, const SweepArgs &a, int nwaves,
     if (nwaves < 1 || nwaves > max_waves_for(NSLOT, vps, p.prior != nullptr))
         return hipErrorInvalidValue;
     if (a.nblk < 1 || a.r0 < 0 || a.r0 + a.nblk > a.R) return hipErrorInvalidValue;
-    if (p.prior && p.emis)
-        hipLaunchKernelGGL((sweep_kernel<PT, NSLOT, 1, false, true, true>), dim3(a.nblk),
-                           dim3(64 * nwaves), 0, st, p.Hr, (const PT::T *)p.emis, p.lu_prefix,
-                           p.prior, p.rho, p.coef, p.recipients, (PT::ST *)p.state, p.log_scale,
-                           p.status, (PT::IO *)p.snap, a);
-    else if (p.prior)
-        hipLaunchKernelGGL((sweep_kernel<PT, NSLOT, 1, false, false, true>), dim3(a.nblk),
-                           dim3(64 * nwaves), 0, st, p.Hr, nullptr, nullptr, p.prior, p.rho,
-                           p.coef, p.recipients, (PT::ST *)p.state, p.log_scale, p.status,
-                           (PT::IO *)p.snap, a);
-    else if (p.emis)
-        hipLaunchKernelGGL((sweep_kernel<PT, NSLOT, 1, false, true>), dim3(a.nblk),
-                           dim3(64 * nwaves), 0, st, p.Hr, (const PT::T *)p.emis, p.lu_prefix, nullptr,
-                           p.rho, p.coef, p.recipients, (PT::ST *)p.state, p.log_scale, p.status,
-                           (PT::IO *)p.snap, a);
-    else
-        hipLaunchKernelGGL((sweep_kernel<PT, NSLOT, 1>), dim3(a.nblk), dim3(64 * nwaves), 0, st,
-                           p.Hr, nullptr, nullptr, nullptr, p.rho, p.coef, p.recipients, (PT::ST *)p.state,
-                           p.log_scale, p.status, (PT::IO *)p.snap, a);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(a.nblk), dim3(64 * nwaves), 0, st, p.Hr,
+                           (const PT::T *)p.emis, p.lu_prefix, p.prior, p.rho, p.coef, p.recipients,
+                           (PT::ST *)p.state, p.log_scale, p.status, (PT::IO *)p.snap, a);
+    };
+    auto pick = [&](auto one) {
+        constexpr bool ONE = decltype(one)::value;
+        if (p.prior && p.emis) go(&sweep_kernel<PT, NSLOT, 1, false, true, true, ONE>);
+        else if (p.prior) go(&sweep_kernel<PT, NSLOT, 1, false, false, true, ONE>);
+        else if (p.emis) go(&sweep_kernel<PT, NSLOT, 1, false, true, false, ONE>);
+        else go(&sweep_kernel<PT, NSLOT, 1, false, false, false, ONE>);
+    };
+    if constexpr (NSLOT <= kOneWaveSlots) {
+        if (nwaves == 1) pick(std::true_type{});
+        else pick(std::false_type{});
+    } else {
+        pick(std::false_type{});
+    }
     return hipGetLastError();
 }
 

@@ -965,6 +965,7 @@ ls_status loglik_grad_impl(const ls_model *m, const int32_t *recipients, int32_t
     ga.prior = m->prior;
     ga.ws = ws;
     ga.lay = lay;
+    lsk::plan_grad_class(ga, (int)prec);
     return dev(lsk::launch_grad(ga, (int)prec, sh, loglik, pac, grad_rho, grad_mu, st,
                                 static_cast<lsk::GradPhase>(phase)));
 }

@@ -110,4 +110,8 @@ inline hipError_t launch_csweep(int prec, const SweepPtrs &p, const ClassPtrs &c
                             : launch_csweep_f32_e(p, c, a, st);
 }
 
+// Shape and checkpoints of the class gradient for this workspace into
+// ga.cg_* (cg_nslot = 0: the plain adjoint).
+void plan_grad_class(GradArgs &ga, int prec);
+
 }  // namespace lsk

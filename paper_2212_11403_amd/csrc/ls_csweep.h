@@ -353,7 +353,7 @@ csweep_kernel(const uint32_t *__restrict__ ids, const uint64_t *__restrict__ key
     };
     // theta^l and the new sum
     auto emit = [&](int l, const uint64_t (&w)[KS], T rr) __attribute__((always_inline)) {
-        const uint64_t fl = (own_key >> (l & (B - 1))) & 1ull ? ~0ull : 0ull;
+        const uint64_t fl = uniform((int)((own_key >> (l & (B - 1))) & 1ull)) ? ~0ull : 0ull;
         const T rv = MUV ? in_vgpr(rr) : r_fix;
         pair_scale_all<KS>(P, Q, w, fl, rv);
         Sprev = S;

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "ls_class.h"
+#include "ls_grad_class.h"
 #include "ls_grad_kernel.h"
 
 namespace lsk {
@@ -100,6 +101,43 @@ static hipError_t dispatch_grad_seg(int prec, const GradArgs &ga, const GradSegA
     if (prec == 0)
         return narrow ? grad_seg_f64_narrow(ga, sa, sh, st) : grad_seg_f64_wide(ga, sa, sh, st);
     return narrow ? grad_seg_f32_narrow(ga, sa, sh, st) : grad_seg_f32_wide(ga, sa, sh, st);
+}
+
+hipError_t launch_grad_class_f32(const GradArgs &ga, const GradClassArgs &a, int nslot, int nwaves,
+                                 hipStream_t st);
+hipError_t launch_grad_class_f64(const GradArgs &ga, const GradClassArgs &a, int nslot, int nwaves,
+                                 hipStream_t st);
+
+// The adjoint of the classes reads the forward vector at every block end. The
+// checkpoint and segment arrays of the workspace hold about 1.5 sqrt(L)
+// vectors per recipient: all block ends if they fit (one launch walks all
+// blocks), else one in `group`, from which the class sweep forms the ends of
+// a group's blocks again before its launch.
+void plan_grad_class(GradArgs &ga, int prec) {
+    ga.cg_nslot = 0;
+    if (!ga.by_class || ga.prior) return;
+    const int vps = prec == 0 ? 2 : 1, ks = ga.cls.kw, words = (ga.N + 63) / 64;
+    if (ks > 8) return;
+    int nslot = 0, nwaves = 0;
+    for (int nw = 1; nw <= kGradClassMaxWaves && !nslot; ++nw) {
+#define LS_MATCH(n) \
+    if (!nslot && nw * n >= words && grad_class_exists(n, ks, vps)) nslot = n, nwaves = nw;
+        LS_MENU_GCLASS(LS_MATCH)
+#undef LS_MATCH
+    }
+    const size_t es = prec == 0 ? 8 : 4;
+    if (!nslot || grad_class_lds(ks, ga.cls.lb, nwaves, es) > 128 * 1024) return;
+    const size_t vec = es * (size_t)ga.R * (size_t)ga.N;
+    const int64_t room = (int64_t)((ga.lay.off_cval - ga.lay.off_ckpt) / vec);
+    const int32_t nb = (ga.L + (1 << ga.cls.lb) - 1) >> ga.cls.lb;
+    int32_t group = 1;
+    if (nb - 1 > room)
+        for (group = 2; group <= kMaxTargets && (nb - 1) / group + group - 1 > room;) ++group;
+    if (group > kMaxTargets) return;
+    ga.cg_nslot = nslot;
+    ga.cg_nwaves = nwaves;
+    ga.cg_blocks = nb;
+    ga.cg_group = group;
 }
 
 // Deterministic sums over recipients: grad_rho[l] = sum_r grow[l][r] (one
@@ -195,16 +233,21 @@ hipError_t launch_grad(const GradArgs &ga, int prec, Shape sh, double *loglik, d
         // log P is bit-identical to that of the log-likelihood alone. A launch
         // holds at most chunk / seg + 1 <= sqrt(chunk) + 1 checkpoints (with an
         // oversized chunk, a launch ends at its 256th checkpoint).
+        // The class adjoint takes the ends of (groups of) blocks instead.
         std::vector<int32_t> tl(2 * kMaxTargets);
         int l0 = -1, knext = 0;
+        const int kept = ga.cg_nslot ? (ga.cg_blocks - 1) / ga.cg_group : ga.nseg;
+        auto kept_at = [&](int k) {
+            return ga.cg_nslot ? (((k + 1) * ga.cg_group) << ga.cls.lb) - 1 : k * ga.seg;
+        };
         while (l0 < ga.L - 1) {
             int t = forward_chunk_end(l0, ga.L - 1, ga.chunk, ga.by_class ? ga.cls.lb : 0);
             int nt = 0;
-            for (; knext < ga.nseg && knext * ga.seg <= t && nt < kMaxTargets; ++knext, ++nt) {
-                tl[2 * nt] = knext * ga.seg;
+            for (; knext < kept && kept_at(knext) <= t && nt < kMaxTargets; ++knext, ++nt) {
+                tl[2 * nt] = kept_at(knext);
                 tl[2 * nt + 1] = knext;
             }
-            if (knext < ga.nseg && knext * ga.seg <= t) t = tl[2 * (nt - 1)];
+            if (knext < kept && kept_at(knext) <= t) t = tl[2 * (nt - 1)];
             e = sweep(0, l0, t, tl.data(), nt, fstate, ws + Ly.off_ckpt, ll);
             if (e != hipSuccess) return e;
             l0 = t;
@@ -213,7 +256,51 @@ hipError_t launch_grad(const GradArgs &ga, int prec, Shape sh, double *loglik, d
     }
     // 2. segments from the last to the first
     double *scratch = reinterpret_cast<double *>(ws + Ly.off_lsc);
-    for (int k = ga.nseg - 1; k >= 0; --k) {
+    if (ga.cg_nslot) {
+        const int lb = ga.cls.lb, G = ga.cg_group, nb = ga.cg_blocks;
+        const int kept = (nb - 1) / G;
+        GradClassArgs ca;
+        ca.N = ga.N;
+        ca.L = ga.L;
+        ca.R = ga.R;
+        ca.lb = lb;
+        ca.th_mis = em.mis;
+        ca.inv_mu = 1.0 / ga.mu;
+        ca.inv_omu = 1.0 / (1.0 - ga.mu);
+        auto adjoint = [&]() {
+            return prec == 0 ? launch_grad_class_f64(ga, ca, ga.cg_nslot, ga.cg_nwaves, st)
+                             : launch_grad_class_f32(ga, ca, ga.cg_nslot, ga.cg_nwaves, st);
+        };
+        if (G == 1) {  // every block end was kept: that of block m in vector m
+            ca.m_lo = ca.vec_lo = ca.vec_up = 0;
+            ca.m_hi = nb - 1;
+            if ((e = adjoint()) != hipSuccess) return e;
+        } else {
+            std::vector<int32_t> tl(2 * kMaxTargets);
+            for (int q = kept; q >= 0; --q) {
+                ca.m_lo = q * G;
+                ca.m_hi = std::min(q * G + G - 1, nb - 1);
+                ca.vec_lo = q > 0 ? q - 1 : 0;
+                ca.vec_up = kept;
+                if (ca.m_hi > ca.m_lo) {
+                    for (int m = ca.m_lo; m < ca.m_hi; ++m) {
+                        tl[2 * (m - ca.m_lo)] = ((m + 1) << lb) - 1;
+                        tl[2 * (m - ca.m_lo) + 1] = kept + m - ca.m_lo;
+                    }
+                    if (q > 0) {
+                        e = hipMemcpyAsync(fstate, ws + Ly.off_ckpt + (size_t)(q - 1) * RN * es,
+                                           (size_t)RN * es, hipMemcpyDeviceToDevice, st);
+                        if (e != hipSuccess) return e;
+                    }
+                    e = sweep(0, (ca.m_lo << lb) - 1, (ca.m_hi << lb) - 1, tl.data(),
+                              ca.m_hi - ca.m_lo, fstate, ws + Ly.off_ckpt, scratch);
+                    if (e != hipSuccess) return e;
+                }
+                if ((e = adjoint()) != hipSuccess) return e;
+            }
+        }
+    }
+    for (int k = ga.cg_nslot ? -1 : ga.nseg - 1; k >= 0; --k) {
         const int s0 = k * ga.seg;
         const int s1 = std::min(s0 + ga.seg - 1, ga.L - 1);
         if (s1 > s0) {

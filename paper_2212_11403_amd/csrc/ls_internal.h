@@ -322,6 +322,9 @@ struct GradArgs {
     bool by_class;        // the checkpointing forward runs as a class sweep
     ClassPtrs cls;
     const double *class_lu_prefix;
+    // the adjoint runs per class (ls_grad_class.h): donor words per wave (0:
+    // it does not), waves, blocks, and blocks per kept checkpoint
+    int32_t cg_nslot, cg_nwaves, cg_blocks, cg_group;
     char *ws;
     GradLayout lay;
 };

@@ -110,6 +110,12 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st) {
 // builtin take them directly)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
+// W elements of X as one access: 16 bytes, or a single element (rows that
+// start anywhere)
+template <class X, int W>
+using vec_of = typename std::conditional<
+    W == 1, X __attribute__((ext_vector_type(1))),
+    typename std::conditional<sizeof(X) == 4, f32x4, f64x2>::type>::type;
 
 // ---------------------------------------------------------------------------
 // Posterior rows. One workgroup per row (k, r) = (blockIdx.y, blockIdx.x) of
@@ -152,17 +158,21 @@ posterior_rows_kernel(const A *alpha, const B *__restrict__ beta, const int32_t 
 }
 
 // The same rows with the products alpha_j beta_j held in registers, for
-// N <= 1024 K W (W = 16 / sizeof(T) elements per 16-byte vector, N, ts and
-// rs multiples of W): alpha and beta are read once, with 16-byte loads, and
-// P / E are written with streaming stores. One workgroup of 1024 threads per
-// row; each thread keeps the products of the entries it writes.
-template <class T, int K>
+// N <= 1024 K W: alpha and beta are read once, with 16-byte loads (W elements;
+// N, ts and rs multiples of W) or one element at a time (W = 1), and P / E are
+// written with streaming stores. One workgroup of 1024 threads per row; each
+// thread keeps the products of the entries it writes. Bound by memory: 16 B per
+// FP32 entry with both outputs. Reading the rows a second time for the outputs
+// costs a quarter of the time at N = 4,999 (2,000 rows x 7 targets, E alone:
+// 233 -> 178 us with W = 1). Longer rows keep the two-pass form: at
+// N = 100,000 the products of a row take 100 registers a thread, which spills
+// (695 us for 1,024 rows against 628).
+template <class T, int K, int W>
 __global__ void __launch_bounds__(1024)
 posterior_rows_reg_kernel(const T *alpha, const T *__restrict__ beta,
                           const int32_t *__restrict__ recips, int32_t R, int64_t ts, int64_t rs,
                           int32_t N, T *P, T *E) {
-    using V = typename std::conditional<sizeof(T) == 4, f32x4, f64x2>::type;
-    constexpr int W = 16 / (int)sizeof(T);
+    using V = vec_of<T, W>;
     __shared__ T red[16];
     const int r = blockIdx.x;
     const int64_t k = blockIdx.y;
@@ -232,23 +242,30 @@ hipError_t launch_posterior_rows(const void *alpha, int alpha_half, const void *
     if (R <= 0 || T <= 0) return hipSuccess;
     if (T > 65535) return hipErrorInvalidValue;
     const dim3 grid((unsigned)R, (unsigned)T), block(256);
-    // rows that fit the register kernel: full-precision inputs, N and the
-    // strides multiples of the vector width, at most 16 elements per thread,
-    // 16-byte aligned
+    // rows that fit the register kernel: full-precision inputs and at most 32
+    // values per thread (16 where they are read one at a time); 16-byte
+    // accesses need N and the strides to be multiples of the vector and every
+    // array to start on 16 bytes
     auto aligned = [](const void *x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
     const int w = is_f64 ? 2 : 4;
-    const bool reg = !alpha_half && !beta_half && N % w == 0 && ts % w == 0 && rs % w == 0 &&
-                     N <= 1024 * 16 && aligned(alpha) && aligned(beta) && aligned(P) &&
-                     aligned(E);
-    if (reg) {
-        if (is_f64)
-            hipLaunchKernelGGL((posterior_rows_reg_kernel<double, 8>), grid, dim3(1024), 0, st,
-                               (const double *)alpha, (const double *)beta, recips, R, ts, rs, N,
-                               (double *)P, (double *)E);
-        else
-            hipLaunchKernelGGL((posterior_rows_reg_kernel<float, 4>), grid, dim3(1024), 0, st,
-                               (const float *)alpha, (const float *)beta, recips, R, ts, rs, N,
-                               (float *)P, (float *)E);
+    const bool vec = N % w == 0 && ts % w == 0 && rs % w == 0 && aligned(alpha) && aligned(beta) &&
+                     aligned(P) && aligned(E);
+    const int per = vec ? (N + 1024 * w - 1) / (1024 * w) : (N + 1023) / 1024;  // accesses a thread
+    if (!alpha_half && !beta_half && per <= (vec ? 8 : 16)) {
+        auto go = [&](auto kern, auto x) {
+            using T_ = decltype(x);
+            hipLaunchKernelGGL(kern, grid, dim3(1024), 0, st, (const T_ *)alpha, (const T_ *)beta,
+                               recips, R, ts, rs, N, (T_ *)P, (T_ *)E);
+        };
+        if (is_f64) {
+            if (!vec) go(&posterior_rows_reg_kernel<double, 16, 1>, 0.0);
+            else go(&posterior_rows_reg_kernel<double, 8, 2>, 0.0);
+        } else {
+            if (!vec && per <= 8) go(&posterior_rows_reg_kernel<float, 8, 1>, 0.0f);
+            else if (!vec) go(&posterior_rows_reg_kernel<float, 16, 1>, 0.0f);
+            else if (per <= 4) go(&posterior_rows_reg_kernel<float, 4, 4>, 0.0f);
+            else go(&posterior_rows_reg_kernel<float, 8, 4>, 0.0f);
+        }
         return hipGetLastError();
     }
     if (is_f64) {
@@ -272,9 +289,12 @@ hipError_t launch_posterior_rows(const void *alpha, int alpha_half, const void *
 // Workgroup (p, k) owns the tile pair (by, bx) / (bx, by), by <= bx, of
 // matrix k, where p counts the pairs of the upper triangle row by row: it
 // reads both 64 x 64 tiles into LDS before writing either, so no other
-// workgroup touches them and D may alias E. With VEC (N a multiple of the
-// 16-byte vector) every lane moves 16 bytes per load and store; D is written
-// with streaming stores (it is not read again here).
+// workgroup touches them and D may alias E. Every lane moves 16 bytes per load
+// and store (W elements) if N is a multiple of the vector, else one element; all
+// its loads are in flight before the first wait either way (N = 4,999, 7 FP32
+// matrices: 605 -> 322 us with W = 1; with two LDS tiles filled row after row
+// before). D is written with
+// streaming stores (it is not read again here).
 __device__ __forceinline__ void tile_pair(int64_t p, int nb, int &by, int &bx) {
     // first pair of row b: b nb - b (b - 1) / 2
     const double a = 2.0 * nb + 1.0;
@@ -286,100 +306,79 @@ __device__ __forceinline__ void tile_pair(int64_t p, int nb, int &by, int &bx) {
     bx = b + (int)(p - first(b));
 }
 
-template <class X, bool VEC>
+template <class X, int W>
 __global__ void __launch_bounds__(256)
 symmetrise_kernel(const X *E, X *D, int32_t N, int32_t nb) {
-    using V = typename std::conditional<sizeof(X) == 4, f32x4, f64x2>::type;
-    constexpr int W = 16 / (int)sizeof(X);  // elements per vector
+    using V = vec_of<X, W>;
     int by, bx;
     tile_pair(blockIdx.x, nb, by, bx);
     __shared__ X ta[64][65];
-    __shared__ X tb[VEC ? 1 : 64][65];
     const int64_t base = (int64_t)blockIdx.y * N * N;
     const int r0 = by * 64, c0 = bx * 64;
-    if constexpr (VEC) {
-        // lane: W consecutive columns of one row; RP rows per pass, IT passes.
-        // All loads of a lane are issued before the first wait; tiles fully
-        // inside the matrix (all but the last tile row and column) skip the
-        // bounds checks.
-        constexpr int CV = 64 / W, RP = 256 / CV, IT = 64 / RP;
-        const int cv = threadIdx.x % CV, rp = threadIdx.x / CV, cc = cv * W;
-        const bool full = r0 + 64 <= N && c0 + 64 <= N;
-        const X *ea = E + base + (int64_t)(r0 + rp) * N + c0 + cc;
-        const X *eb = E + base + (int64_t)(c0 + rp) * N + r0 + cc;
-        V va[IT], vb[IT];
-        if (full) {
+    // lane: W consecutive columns of one row; RP rows per pass, IT passes.
+    // All loads of a lane are issued before the first wait; tiles fully
+    // inside the matrix (all but the last tile row and column) skip the
+    // bounds checks.
+    constexpr int CV = 64 / W, RP = 256 / CV, IT = 64 / RP;
+    const int cv = threadIdx.x % CV, rp = threadIdx.x / CV, cc = cv * W;
+    const bool full = r0 + 64 <= N && c0 + 64 <= N;
+    const X *ea = E + base + (int64_t)(r0 + rp) * N + c0 + cc;
+    const X *eb = E + base + (int64_t)(c0 + rp) * N + r0 + cc;
+    V va[IT], vb[IT];
+    if (full) {
 #pragma unroll
-            for (int it = 0; it < IT; ++it) {
-                va[it] = *reinterpret_cast<const V *>(ea + (int64_t)it * RP * N);
-                vb[it] = *reinterpret_cast<const V *>(eb + (int64_t)it * RP * N);
-            }
-        } else {
-#pragma unroll
-            for (int it = 0; it < IT; ++it) {
-                const int rr = rp + it * RP;
-                va[it] = (r0 + rr < N && c0 + cc < N)
-                             ? *reinterpret_cast<const V *>(ea + (int64_t)it * RP * N)
-                             : V{};
-                vb[it] = (c0 + rr < N && r0 + cc < N)
-                             ? *reinterpret_cast<const V *>(eb + (int64_t)it * RP * N)
-                             : V{};
-            }
+        for (int it = 0; it < IT; ++it) {
+            va[it] = *reinterpret_cast<const V *>(ea + (int64_t)it * RP * N);
+            vb[it] = *reinterpret_cast<const V *>(eb + (int64_t)it * RP * N);
         }
-        // Both tiles are now in registers, so D (which may alias E) can be
-        // written at once. The transposed operand goes through one LDS tile
-        // used twice: tile b for the first output, then tile a.
+    } else {
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int rr = rp + it * RP;
+            va[it] = (r0 + rr < N && c0 + cc < N)
+                         ? *reinterpret_cast<const V *>(ea + (int64_t)it * RP * N)
+                         : V{};
+            vb[it] = (c0 + rr < N && r0 + cc < N)
+                         ? *reinterpret_cast<const V *>(eb + (int64_t)it * RP * N)
+                         : V{};
+        }
+    }
+    // Both tiles are now in registers, so D (which may alias E) can be
+    // written at once. The transposed operand goes through one LDS tile
+    // used twice: tile b for the first output, then tile a.
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int k = 0; k < W; ++k) ta[rp + it * RP][cc + k] = vb[it][k];
+    __syncthreads();
+    X *da = D + base + (int64_t)(r0 + rp) * N + c0 + cc;
+    X *db = D + base + (int64_t)(c0 + rp) * N + r0 + cc;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int rr = rp + it * RP;
+        V o;
+#pragma unroll
+        for (int k = 0; k < W; ++k)
+            o[k] = (r0 + rr == c0 + cc + k) ? (X)0 : va[it][k] + ta[cc + k][rr];
+        if (full || (r0 + rr < N && c0 + cc < N))
+            __builtin_nontemporal_store(o, reinterpret_cast<V *>(da + (int64_t)it * RP * N));
+    }
+    if (by != bx) {
+        __syncthreads();
 #pragma unroll
         for (int it = 0; it < IT; ++it)
 #pragma unroll
-            for (int k = 0; k < W; ++k) ta[rp + it * RP][cc + k] = vb[it][k];
+            for (int k = 0; k < W; ++k) ta[rp + it * RP][cc + k] = va[it][k];
         __syncthreads();
-        X *da = D + base + (int64_t)(r0 + rp) * N + c0 + cc;
-        X *db = D + base + (int64_t)(c0 + rp) * N + r0 + cc;
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
             const int rr = rp + it * RP;
             V o;
 #pragma unroll
-            for (int k = 0; k < W; ++k)
-                o[k] = (r0 + rr == c0 + cc + k) ? (X)0 : va[it][k] + ta[cc + k][rr];
-            if (full || (r0 + rr < N && c0 + cc < N))
-                __builtin_nontemporal_store(o, reinterpret_cast<V *>(da + (int64_t)it * RP * N));
-        }
-        if (by != bx) {
-            __syncthreads();
-#pragma unroll
-            for (int it = 0; it < IT; ++it)
-#pragma unroll
-                for (int k = 0; k < W; ++k) ta[rp + it * RP][cc + k] = va[it][k];
-            __syncthreads();
-#pragma unroll
-            for (int it = 0; it < IT; ++it) {
-                const int rr = rp + it * RP;
-                V o;
-#pragma unroll
-                for (int k = 0; k < W; ++k) o[k] = vb[it][k] + ta[cc + k][rr];
-                if (full || (c0 + rr < N && r0 + cc < N))
-                    __builtin_nontemporal_store(o,
-                                                reinterpret_cast<V *>(db + (int64_t)it * RP * N));
-            }
-        }
-    } else {
-        const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 64 x 4
-        // ta = E[r0.., c0..], tb = E[c0.., r0..]
-        for (int rr = ty; rr < 64; rr += 4) {
-            const int r = r0 + rr, c = c0 + tx;
-            ta[rr][tx] = (r < N && c < N) ? E[base + (int64_t)r * N + c] : (X)0;
-            const int r2 = c0 + rr, c2 = r0 + tx;
-            tb[rr][tx] = (r2 < N && c2 < N) ? E[base + (int64_t)r2 * N + c2] : (X)0;
-        }
-        __syncthreads();
-        for (int rr = ty; rr < 64; rr += 4) {
-            const int r = r0 + rr, c = c0 + tx;
-            if (r < N && c < N) D[base + (int64_t)r * N + c] = (r == c) ? (X)0 : ta[rr][tx] + tb[tx][rr];
-            const int r2 = c0 + rr, c2 = r0 + tx;
-            if (by != bx && r2 < N && c2 < N)
-                D[base + (int64_t)r2 * N + c2] = tb[rr][tx] + ta[tx][rr];
+            for (int k = 0; k < W; ++k) o[k] = vb[it][k] + ta[cc + k][rr];
+            if (full || (c0 + rr < N && r0 + cc < N))
+                __builtin_nontemporal_store(o,
+                                            reinterpret_cast<V *>(db + (int64_t)it * RP * N));
         }
     }
 }
@@ -397,20 +396,16 @@ hipError_t launch_symmetrise(const void *E, void *D, int32_t N, int32_t T, int i
     const int w = is_f64 ? 2 : 4;
     const bool vec = N % w == 0 && (reinterpret_cast<uintptr_t>(E) & 15) == 0 &&
                      (reinterpret_cast<uintptr_t>(D) & 15) == 0;
+    auto go = [&](auto kern, auto x) {
+        using X = decltype(x);
+        hipLaunchKernelGGL(kern, grid, block, 0, st, (const X *)E, (X *)D, N, nb);
+    };
     if (is_f64) {
-        if (vec)
-            hipLaunchKernelGGL((symmetrise_kernel<double, true>), grid, block, 0, st,
-                               (const double *)E, (double *)D, N, nb);
-        else
-            hipLaunchKernelGGL((symmetrise_kernel<double, false>), grid, block, 0, st,
-                               (const double *)E, (double *)D, N, nb);
+        if (vec) go(&symmetrise_kernel<double, 2>, 0.0);
+        else go(&symmetrise_kernel<double, 1>, 0.0);
     } else {
-        if (vec)
-            hipLaunchKernelGGL((symmetrise_kernel<float, true>), grid, block, 0, st,
-                               (const float *)E, (float *)D, N, nb);
-        else
-            hipLaunchKernelGGL((symmetrise_kernel<float, false>), grid, block, 0, st,
-                               (const float *)E, (float *)D, N, nb);
+        if (vec) go(&symmetrise_kernel<float, 4>, 0.0f);
+        else go(&symmetrise_kernel<float, 1>, 0.0f);
     }
     return hipGetLastError();
 }

@@ -413,13 +413,18 @@ hipError_t launch_symmetrise(const void *E, void *D, int32_t N, int32_t T, int i
 // ---------------------------------------------------------------------------
 // Emission tables of a per-variant mu, from (1-H)(1-2mu)+mu (appendix A.3) in
 // FP64: the FP64 pair as is; the FP32 pair divided by its larger member and
-// rounded once, with the log of that divisor (all threads, into
-// lu_prefix[l+1]); then the prefix sums of those logs in index order (one
-// thread, so the sums are fixed).
-__global__ void __launch_bounds__(256)
+// rounded once; and the prefix sums of the log of that divisor. One workgroup:
+// each thread sums the logs of a run of variants, the run totals are added in a
+// fixed tree, and each thread continues its run from the total before it (one
+// thread adding all L logs took 254 us at L = 2,000).
+__global__ void __launch_bounds__(1024)
 emission_tables_kernel(const double *__restrict__ mu_vec, int32_t L, double *__restrict__ em64,
                        float *__restrict__ em32, double *__restrict__ lu_prefix) {
-    for (int l = threadIdx.x; l < L; l += 256) {
+    __shared__ double tot[1024];
+    const int run = (L + 1023) / 1024;
+    const int a = min(L, (int)threadIdx.x * run), b = min(L, a + run);
+    double s = 0.0;
+    for (int l = a; l < b; ++l) {
         const double mu = mu_vec[l];
         const double omu = (1.0 - 2.0 * mu) + mu;
         em64[2 * l] = omu;
@@ -427,22 +432,29 @@ emission_tables_kernel(const double *__restrict__ mu_vec, int32_t L, double *__r
         const double unit = omu >= mu ? omu : mu;
         em32[2 * l] = (float)(omu / unit);
         em32[2 * l + 1] = (float)(mu / unit);
-        lu_prefix[l + 1] = log(unit);
+        const double lu = log(unit);
+        lu_prefix[l + 1] = lu;
+        s += lu;
     }
+    tot[threadIdx.x] = s;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double acc = 0.0;
-        lu_prefix[0] = 0.0;
-        for (int l = 0; l < L; ++l) {
-            acc += lu_prefix[l + 1];
-            lu_prefix[l + 1] = acc;
-        }
+    for (int h = 1; h < 1024; h *= 2) {
+        const double x = (int)threadIdx.x >= h ? tot[threadIdx.x - h] : 0.0;
+        __syncthreads();
+        tot[threadIdx.x] += x;
+        __syncthreads();
+    }
+    s = threadIdx.x > 0 ? tot[threadIdx.x - 1] : 0.0;
+    if (threadIdx.x == 0) lu_prefix[0] = 0.0;
+    for (int l = a; l < b; ++l) {
+        s += lu_prefix[l + 1];
+        lu_prefix[l + 1] = s;
     }
 }
 
 hipError_t launch_emission_tables(const double *mu_vec, int32_t L, double *em64, float *em32,
                                   double *lu_prefix, hipStream_t st) {
-    hipLaunchKernelGGL(emission_tables_kernel, dim3(1), dim3(256), 0, st, mu_vec, L, em64, em32,
+    hipLaunchKernelGGL(emission_tables_kernel, dim3(1), dim3(1024), 0, st, mu_vec, L, em64, em32,
                        lu_prefix);
     return hipGetLastError();
 }
@@ -527,12 +539,12 @@ hipError_t launch_calc_rho(const double *cM, int32_t n, double s, double gamma, 
 // (0 where m_l = 0); out = {sum_l g_l d rho_l / d s, sum_l g_l d rho_l / d gamma}.
 // One workgroup: per-thread strided sums in index order, then a fixed tree,
 // so the result does not depend on scheduling.
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 rho_map_grad_kernel(const double *__restrict__ cM, int32_t n, double s, double gamma,
                     const double *__restrict__ g, double *__restrict__ out) {
-    __shared__ double ps[256], pg[256];
+    __shared__ double ps[1024], pg[1024];
     double as = 0.0, ag = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) {
+    for (int i = threadIdx.x; i < n; i += 1024) {
         const double m = cM[i] / 100.0;
         if (m > 0.0) {
             const double mg = pow(m, gamma);
@@ -544,7 +556,7 @@ rho_map_grad_kernel(const double *__restrict__ cM, int32_t n, double s, double g
     ps[threadIdx.x] = as;
     pg[threadIdx.x] = ag;
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
+    for (int h = 512; h > 0; h >>= 1) {
         if ((int)threadIdx.x < h) {
             ps[threadIdx.x] += ps[threadIdx.x + h];
             pg[threadIdx.x] += pg[threadIdx.x + h];
@@ -559,7 +571,7 @@ rho_map_grad_kernel(const double *__restrict__ cM, int32_t n, double s, double g
 
 hipError_t launch_rho_map_grad(const double *cM, int32_t n, double s, double gamma,
                                const double *g, double *out, hipStream_t st) {
-    hipLaunchKernelGGL(rho_map_grad_kernel, dim3(1), dim3(256), 0, st, cM, n, s, gamma, g, out);
+    hipLaunchKernelGGL(rho_map_grad_kernel, dim3(1), dim3(1024), 0, st, cM, n, s, gamma, g, out);
     return hipGetLastError();
 }
 

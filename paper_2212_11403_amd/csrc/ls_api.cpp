@@ -248,7 +248,9 @@ double plain_step_cost(int32_t N) {
 int32_t choose_classes(int32_t N, const int32_t most[3]) {
     double best = 0.8 * plain_step_cost(N);
     int32_t pick = 0;
-    for (int b = 0; b < 3; ++b) {
+    // from the longest blocks down: a shorter one has to save 5% (its
+    // boundaries also cost checkpoints in the gradient)
+    for (int b = 2; b >= 0; --b) {
         if (most[b] > lsk::class_cap(N)) continue;
         int kw = 0, ns = 0, nw = 0;
         const int need = (most[b] + 63) / 64;
@@ -258,7 +260,7 @@ int32_t choose_classes(int32_t N, const int32_t most[3]) {
 #undef LS_MATCH
         if (kw == 0 || 64 * kw > lsk::class_cap(N) || !class_shape(N, LS_FP32, kw, &ns, &nw)) continue;
         const double c = class_step_cost(N, 4 + b, kw);
-        if (c < best) {
+        if (c < (pick ? 0.95 : 1.0) * best) {
             best = c;
             pick = (4 + b) | (kw << 8);
         }

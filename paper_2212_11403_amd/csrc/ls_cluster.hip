@@ -22,14 +22,14 @@
 // that distance, and were it below i, it would itself be at that distance and
 // come before i. So a merge looks for the first smallest nd only.
 //
-// What bounds it: the chain of one merge, a handful of barriers and two
-// round trips to memory (rows a and b; the rescanned rows). Distances are
+// What bounds it: the chain of one merge, a handful of barriers and a round
+// trip to memory (rows a and b, with the first four rescanned rows). Distances are
 // compared as integers that order like them, so a wave finds a minimum with
 // one DPP instruction per step; rows are rescanned four at a time by the whole
 // workgroup, so their loads are in flight together; the barriers inside a
 // merge wait for local memory only, and the one before the next merge also
-// for the stores to D. Six FP32 matrices of N = 3,000: 22.0 ms, 7.3 us per
-// merge (74.9 ms with pairs compared through shuffles, full barriers and one
+// for the stores to D. Six FP32 matrices of N = 3,000: 20.7 ms, 6.9 us per
+// merge (22.0 with the rescanned rows read after the update; 74.9 with pairs compared through shuffles, full barriers and one
 // rescanned row after another).
 #include <math.h>
 
@@ -252,27 +252,55 @@ linkage_kernel(T *__restrict__ D, int32_t N, size_t ws_stride, char *ws, double 
         const int na = size[a], nb = size[b];
         const int ida = tid == 0 ? id[a] : 0, idb = tid == 0 ? id[b] : 0;
         const T fa = (T)na, fb = (T)nb, fn = (T)(na + nb);
-        // row and column a of the merged cluster; rows whose nearest slot was
-        // a or b are listed for a rescan (their nd then holds the new distance
-        // to a), the others compare with it
+        // Rows whose nearest slot was a or b are listed for a rescan. The list
+        // needs local memory only, so the first listed rows are read together
+        // with rows a and b: one round trip to memory in place of two.
         T *ra = Dm + (int64_t)a * N;
         const T *rb = Dm + (int64_t)b * N;
         int *const nl = &nlist[m & 1];
+        constexpr int U = sizeof(T) == 4 ? 4 : 2;  // slots of a thread read ahead
+        T xa[U], xb[U], x0[ROWS][U];
+        bool on[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = tid + u * nth;
+            on[u] = q < N && nn[q < N ? q : 0] != kEmptySlot && q != a && q != b;
+            xa[u] = on[u] ? ra[q] : (T)0;
+            xb[u] = on[u] ? rb[q] : (T)0;
+        }
+        for (int k = tid; k < N; k += nth) {
+            const Slot j = nn[k];
+            if (j != kEmptySlot && k != a && k != b && ((int)j == a || (int)j == b))
+                list[atomicAdd(nl, 1)] = (Slot)k;
+        }
+        barrier();
+        const int nf = *nl;
+        int row[ROWS];
+        auto rows_of = [&](int f0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) row[r] = (int)list[f0 + r < nf ? f0 + r : f0];
+        };
+        if (nf > 0) {
+            rows_of(0);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    x0[r][u] = on[u] ? Dm[(int64_t)row[r] * N + tid + u * nth] : (T)0;
+        }
+        // row and column a of the merged cluster; a listed row's nd then holds its
+        // new distance to a, the others compare with it
         Best<T> ca;
         T da = (T)0;
-        auto update = [&](int k, T xa, T xb) __attribute__((always_inline)) {
-            const T x = fa * xa;
-            const T y = fb * xb;
+        auto update = [&](int k, T va, T vb) __attribute__((always_inline)) {
+            const T x = fa * va;
+            const T y = fb * vb;
             const T s = x + y;
             const T d = s / fn;
             ra[k] = d;
             Dm[(int64_t)k * N + a] = d;
             const int j = (int)nn[k];
-            if (j == a || j == b) {
-                list[atomicAdd(nl, 1)] = (Slot)k;
-                nd[k] = d;
-                nn[k] = (Slot)a;
-            } else if (before(d, a, nd[k], j)) {
+            if (j == a || j == b || before(d, a, nd[k], j)) {
                 nn[k] = (Slot)a;
                 nd[k] = d;
             }
@@ -283,23 +311,10 @@ linkage_kernel(T *__restrict__ D, int32_t N, size_t ws_stride, char *ws, double 
                 da = d;
             }
         };
-        constexpr int U = 4;
-        int k = tid;
-        for (; k + (U - 1) * nth < N; k += U * nth) {
-            T xa[U], xb[U];
-            bool on[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int q = k + u * nth;
-                on[u] = nn[q] != kEmptySlot && q != a && q != b;
-                xa[u] = on[u] ? ra[q] : (T)0;
-                xb[u] = on[u] ? rb[q] : (T)0;
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (on[u]) update(k + u * nth, xa[u], xb[u]);
-        }
-        for (; k < N; k += nth)
+        for (int u = 0; u < U; ++u)
+            if (on[u]) update(tid + u * nth, xa[u], xb[u]);
+        for (int k = tid + U * nth; k < N; k += nth)
             if (nn[k] != kEmptySlot && k != a && k != b) update(k, ra[k], rb[k]);
         {
             const Best<T> r = wave_best(ca, mine);
@@ -318,43 +333,38 @@ linkage_kernel(T *__restrict__ D, int32_t N, size_t ws_stride, char *ws, double 
             id[a] = N + m;
             nlist[(m + 1) & 1] = 0;
         }
-        barrier();
-        const int nf = *nl;
-        if (wave == nwaves - 1) {  // the nearest slot of the merged row
-            Best<T> r;
-            first_of(wa, r, mine);
-            if (mine) {
-                nn[a] = (Slot)r.slot;
-                nd[a] = wa[lane].d;
-            }
-            if (lane == 0) nn[b] = kEmptySlot;
-        }
-        // rescan the listed rows
+        // rescan the listed rows, slot a apart (its distance is in nd)
         for (int f0 = 0, set = 0; f0 < nf; f0 += ROWS, set ^= 1) {
             Best<T> cr[ROWS];
-            T dr[ROWS], dn[ROWS];
-            int row[ROWS];
+            T dr[ROWS];
+            if (f0 > 0) rows_of(f0);
 #pragma unroll
-            for (int r = 0; r < ROWS; ++r) {
-                row[r] = (int)list[f0 + r < nf ? f0 + r : f0];
-                dr[r] = (T)0;
-                dn[r] = nd[row[r]];
-            }
+            for (int r = 0; r < ROWS; ++r) dr[r] = (T)0;
             auto scan = [&](int q, const T (&x)[ROWS]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int r = 0; r < ROWS; ++r) {
-                    const T d = q == a ? dn[r] : x[r];
-                    const auto key = order_key(d);
+                    const auto key = order_key(x[r]);
                     if (q != row[r] && key < cr[r].key) {
                         cr[r].key = key;
                         cr[r].slot = (uint32_t)q;
-                        dr[r] = d;
+                        dr[r] = x[r];
                     }
                 }
             };
+            int q = tid;
+            if (f0 == 0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    T x[ROWS];
+#pragma unroll
+                    for (int r = 0; r < ROWS; ++r) x[r] = x0[r][u];
+                    if (on[u]) scan(tid + u * nth, x);
+                }
+                q += U * nth;
+            }
 #pragma unroll 2
-            for (int q = tid; q < N; q += nth) {
-                if (nn[q] == kEmptySlot || q == b) continue;
+            for (; q < N; q += nth) {
+                if (nn[q] == kEmptySlot || q == a || q == b) continue;
                 T x[ROWS];
 #pragma unroll
                 for (int r = 0; r < ROWS; ++r) x[r] = Dm[(int64_t)row[r] * N + q];
@@ -375,11 +385,23 @@ linkage_kernel(T *__restrict__ D, int32_t N, size_t ws_stride, char *ws, double 
                 Best<T> best;
                 first_of(rb_[set][r], best, mine);
                 const int k2 = (int)list[f0 + r];
-                if (mine) {
+                const auto key = order_key(nd[k2]);
+                const bool keep = key < best.key || (key == best.key && (uint32_t)a < best.slot);
+                if (mine && !keep) {
                     nn[k2] = (Slot)best.slot;
                     nd[k2] = rb_[set][r][lane].d;
                 }
             }
+        }
+        if (nf == 0) barrier();
+        if (wave == nwaves - 1) {  // the nearest slot of the merged row
+            Best<T> r;
+            first_of(wa, r, mine);
+            if (mine) {
+                nn[a] = (Slot)r.slot;
+                nd[a] = wa[lane].d;
+            }
+            if (lane == 0) nn[b] = kEmptySlot;
         }
         barrier();
     }

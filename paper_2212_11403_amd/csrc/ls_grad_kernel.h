@@ -69,10 +69,9 @@ __host__ __device__ constexpr int grad_kernel_waves(int nslot, int vgpr_per_slot
 // recipient's word, up to 8 row words) while the variant before it is worked
 // on, and keep the sums of a variant in one lane each, so that the FP64 terms
 // (four divisions) are formed for 64 variants at once instead of after every
-// one. The map fit at N = 500, L = 2,000, FP64:
-// 4.83 -> 4.26 ms per step. Groups of
-// several waves form the terms at once, in wave 0, off the path of the others
-// (for them the lanes measured 4 to 6% slower).
+// one. The map fit at N = 500, L = 2,000, FP64: 4.83 -> 4.26 ms per step.
+// Groups of several waves form the terms at once, in wave 0, off the path of
+// the others (for them the lanes measured 4 to 6% slower).
 template <class PT, int NSLOT, bool NARROW, bool MUV = false, bool PI = false, bool ONE = false>
 __global__ void __launch_bounds__(ONE ? 64 : 64 * grad_kernel_waves(NSLOT, PT::vgpr_per_slot, NARROW, PI))
 grad_seg_kernel(const uint64_t *__restrict__ Hr, const double *__restrict__ rho,

@@ -208,58 +208,90 @@ bool choose_shape(int32_t N, int prec, Shape *out, bool grad = false, bool prior
 int class_lb(const ls_model *m) { return m->reserved & 255; }
 int class_words(const ls_model *m) { return (m->reserved >> 8) & 255; }
 
-// Donor words per wave and waves of the class sweep for kw class words: as
-// few waves as place N (one wave steps the classes, the others wait for it),
-// eight at most.
+int class_groups(int nslot, int nwaves, int kw, int vps) {
+    return std::max(1, 4 * lsk::csweep_waves_per_simd(nslot, kw, vps) / nwaves);
+}
+
+// Donor words per wave and waves of the class sweep for kw class words, eight
+// waves at most: most groups on a compute unit, then fewest padded words, then
+// fewest waves (one wave steps the classes, the others wait for it). Padding
+// counts at the block boundaries: at N = 10,000 in FP64, B = 32, four waves of
+// 40 words take 207 ns per step with kw = 6 and three of 64 take 262; at
+// N = 30,000 in FP32, kw = 8, three of 160 take 308 ns and four of 128 take 371;
+// at N = 50,000, kw = 12, seven of 112 take 720 and five of 160 take 883.
 bool class_shape(int32_t N, int prec, int kw, int *nslot, int *nwaves) {
     const int vps = vgpr_per_slot(prec), words = (N + 63) / 64;
+    int groups = 0, slots = 0;
     for (int nw = 1; nw <= 8; ++nw) {
-#define LS_MATCH(n)                                                            \
-    if (nw * n >= words && lsk::csweep_exists(n, kw, vps) && !(vps == 2 && n > 80)) { \
-        *nslot = n;                                                            \
-        *nwaves = nw;                                                          \
-        return true;                                                           \
-    }
+        int ns = 0;
+#define LS_MATCH(n) \
+    if (ns == 0 && nw * n >= words && lsk::csweep_exists(n, kw, vps) && !(vps == 2 && n > 80)) ns = n;
         LS_MENU_CSLOT_A(LS_MATCH)
         LS_MENU_CSLOT_B(LS_MATCH)
         LS_MENU_CSLOT_C(LS_MATCH)
         LS_MENU_CSLOT_D(LS_MATCH)
         LS_MENU_CSLOT_E(LS_MATCH)
 #undef LS_MATCH
+        if (ns == 0) continue;
+        const int g = class_groups(ns, nw, kw, vps);
+        if (g > groups || (g == groups && nw * ns < slots)) {
+            groups = g;
+            slots = nw * ns;
+            *nslot = ns;
+            *nwaves = nw;
+        }
     }
-    return false;
+    return groups > 0;
 }
 
-// Vector instructions of one recipient step: the class sweep's (5 per class
-// word and about 30 around them, and at each block boundary about 10 per
-// donor word, its LDS accesses included) and the plain sweep's (3 per slot
-// and 34 per wave).
-double class_step_cost(int32_t N, int lb, int kw) {
-    return 5.0 * kw + 30.0 + 10.0 * ((N + 63) / 64) / (double)(1 << lb);
+// Time of one recipient step on one compute unit (ns), full GPU, from sweeps
+// measured at N = 1,000 .. 50,000, every block length and 2 to 16 class words
+// (FP32 / FP64). A block boundary is bound by LDS: 19 / 22.5 ns per donor word
+// and block. A class step is a chain of 140 + 28 kw / 250 + 10 kw ns in each of
+// the groups a compute unit holds. The two overlap between groups: the larger
+// plus 0.3 of the smaller from four groups up, 0.5 with two or three, 0.7 with
+// one. Measured / model (ns): N = 10,000 FP32 (B, kw) = (64, 6) 56 / 58,
+// (64, 12) 68 / 74, (32, 12) 119 / 111; FP64 (32, 4) 144 / 132, (32, 6) 207 /
+// 210, (64, 16) 468 / 443; N = 50,000 FP32 (32, 12) 720 / 801, (32, 16) 832 /
+// 914. Below N = 5,000 both sides are bound by the time of a step's chain and
+// come out low alike.
+double class_step_cost(int32_t N, int prec, int lb, int kw) {
+    int ns = 0, nw = 0;
+    if (!class_shape(N, prec, kw, &ns, &nw)) return 1e300;
+    const bool f64 = prec == LS_FP64;
+    const int groups = class_groups(ns, nw, kw, vgpr_per_slot(prec));
+    const double bound = (f64 ? 22.5 : 19.0) * ((N + 63) / 64) / (double)(1 << lb);
+    const double step = (f64 ? 250.0 + 10.0 * kw : 140.0 + 28.0 * kw) / groups;
+    const double lap = groups == 1 ? 0.7 : (groups < 4 ? 0.5 : 0.3);
+    return std::max(bound, step) + lap * std::min(bound, step);
 }
-double plain_step_cost(int32_t N) {
+// The plain sweep: 3 instructions per slot and 34 per wave, at 0.42 ns (FP32;
+// 257 ns at N = 10,000, 498 at 20,000) or 0.62 ns (FP64: 379 and 779).
+double plain_step_cost(int32_t N, int prec) {
     Shape sh;
-    if (!choose_shape(N, LS_FP32, &sh)) return 0.0;
-    return sh.nwaves * (3.0 * sh.nslot + 34.0);
+    if (!choose_shape(N, prec, &sh)) return 0.0;
+    return (prec == LS_FP64 ? 0.62 : 0.42) * sh.nwaves * (3.0 * sh.nslot + 34.0);
 }
 
 // Block length and class words for the largest class counts `most` of blocks
-// of 16, 32 and 64 variants; 0 if the plain sweep is predicted to be as good.
+// of 16, 32 and 64 variants; 0 unless predicted to save 15% of the plain sweep
+// (N = 50,000 with 1,000 founders, blocks of 16 and 16 words: 2,076 ns against
+// the plain 1,454; N = 10,000 FP64, (64, 16): 468 against 379).
 int32_t choose_classes(int32_t N, const int32_t most[3]) {
-    double best = 0.8 * plain_step_cost(N);
+    double best = 0.85 * plain_step_cost(N, LS_FP32);
     int32_t pick = 0;
     // from the longest blocks down: a shorter one has to save 5% (its
     // boundaries also cost checkpoints in the gradient)
     for (int b = 2; b >= 0; --b) {
         if (most[b] > lsk::class_cap(N)) continue;
-        int kw = 0, ns = 0, nw = 0;
+        int kw = 0;
         const int need = (most[b] + 63) / 64;
 #define LS_MATCH(v) \
     if (kw == 0 && v >= need) kw = v;
         LS_MENU_CLASS(LS_MATCH)
 #undef LS_MATCH
-        if (kw == 0 || 64 * kw > lsk::class_cap(N) || !class_shape(N, LS_FP32, kw, &ns, &nw)) continue;
-        const double c = class_step_cost(N, 4 + b, kw);
+        if (kw == 0 || 64 * kw > lsk::class_cap(N)) continue;
+        const double c = class_step_cost(N, LS_FP32, 4 + b, kw);
         if (c < (pick ? 0.95 : 1.0) * best) {
             best = c;
             pick = (4 + b) | (kw << 8);
@@ -276,8 +308,10 @@ constexpr int kClassMinMove = 64;
 bool class_route(const ls_model *m, int prec, int variants) {
     if (class_lb(m) == 0 || m->prior || variants < kClassMinMove) return false;
     if (prec != LS_FP32 && prec != LS_FP64) return false;
-    int ns = 0, nw = 0;
-    if (!class_shape(m->N, prec, class_words(m), &ns, &nw)) return false;
+    // (the block length is chosen for FP32)
+    if (prec == LS_FP64 && class_step_cost(m->N, prec, class_lb(m), class_words(m)) >=
+                               0.85 * plain_step_cost(m->N, prec))
+        return false;
     return std::getenv("LS_FORCE_SHAPE") == nullptr;  // a forced shape is a plain sweep's
 }
 
@@ -578,7 +612,9 @@ ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *str
     if (in_range && !m->mu_vec) in_range = mu_fits(m->mu);
     for (size_t k = 0; in_range && k < muv.size(); ++k) in_range = mu_fits(muv[k]);
     for (size_t k = 0; in_range && k < rho.size(); ++k) in_range = rho[k] <= 0.9;
-    if (in_range) {
+    // (and past N = 81,920 no class sweep holds the donors in registers)
+    int ns = 0, nw = 0;
+    if (in_range && class_shape(m->N, LS_FP32, 2, &ns, &nw)) {
         char *section = static_cast<char *>(workspace) + class_offset_bytes(m->N, m->L);
         const lsk::ClassLayout lay = lsk::class_layout(m->N, m->L);
         int32_t *most = reinterpret_cast<int32_t *>(section + lay.off_max);

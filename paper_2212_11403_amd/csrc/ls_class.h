@@ -27,6 +27,18 @@ constexpr int kClassMaxWords = 16;
 __host__ __device__ constexpr bool csweep_exists(int nslot, int kw, int vgpr_per_slot) {
     return (nslot + 4 * kw) * vgpr_per_slot + (vgpr_per_slot == 2 ? 60 : 45) <= 256;
 }
+// Register need of a class sweep: the donor words, four values per class word
+// and about 45 more; the kernels are compiled for the waves per SIMD it gives.
+__host__ __device__ constexpr int csweep_waves_per_simd(int nslot, int ks, int vgpr_per_slot) {
+    const int need = (nslot + 4 * ks) * vgpr_per_slot + (vgpr_per_slot == 2 ? 60 : 45);
+    const int w = 512 / ((need + 7) / 8 * 8);
+    return w > 8 ? 8 : (w < 1 ? 1 : w);
+}
+__host__ __device__ constexpr int csweep_max_waves(int nslot, int ks, int vgpr_per_slot) {
+    const int w = 4 * csweep_waves_per_simd(nslot, ks, vgpr_per_slot);
+    return w > 8 ? 8 : w;
+}
+
 constexpr int kClassMinB = 16;   // shortest block
 constexpr int kClassMinN = 512;  // below, one wave holds few donors: no gain
 constexpr int kClassMinL = 64;

@@ -19,14 +19,23 @@ __device__ __forceinline__ uint32_t hash_key(uint64_t z) {
 }
 
 // Alleles of donor word * 64 + lane at variants l0 .. l0 + n - 1, variant
-// l0 + b in bit b. `word` is wave-uniform.
+// l0 + b in bit b. `word` is wave-uniform: the rows are scalar loads, eight in
+// flight (one at a time, a wave waits a memory latency per variant), and each
+// is a lane mask as it stands, so a bit takes two instructions. Model set-up at
+// N = 50,000, L = 2,000: 972 us, 1,529 with one load at a time.
 __device__ __forceinline__ uint64_t donor_key(const uint64_t *__restrict__ Hr, int64_t stride,
-                                              int NF, int word, int lane, int l0, int n) {
+                                              int NF, int word, int l0, int n) {
     const uint64_t *p = Hr + (int64_t)l0 * stride + (word < NF ? word : 2 * NF);
     uint64_t key = 0;
-    for (int b = 0; b < n; ++b) {
-        const uint64_t x = p[(int64_t)b * stride];
-        key |= ((x >> lane) & 1ull) << b;
+    for (int b = 0; b < n; b += 8) {
+        uint64_t x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = p[(int64_t)min(b + u, n - 1) * stride];
+        uint32_t bits = 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) bits |= lane_bit(x[u]) ? 1u << u : 0u;
+        if (n - b < 8) bits &= (1u << (n - b)) - 1u;
+        key |= (uint64_t)bits << b;
     }
     return key;
 }
@@ -82,8 +91,8 @@ class_count_kernel(const uint64_t *__restrict__ Hr, int64_t stride, int32_t N, i
     const int lane = threadIdx.x & 63;
     for (int word = uniform(threadIdx.x >> 6); word * 64 < N; word += 16) {
         if (*(volatile int *)&count > cap) break;
-        if (word * 64 + lane < N)
-            find_slot(donor_key(Hr, stride, NF, word, lane, l0, n), tab, HS, cap, &count, &extra);
+        const uint64_t key = donor_key(Hr, stride, NF, word, l0, n);
+        if (word * 64 + lane < N) find_slot(key, tab, HS, cap, &count, &extra);
     }
     __syncthreads();
     if (threadIdx.x == 0) atomicMax(most, count);
@@ -119,9 +128,9 @@ class_build_kernel(const uint64_t *__restrict__ Hr, int64_t stride, int32_t N, i
     auto at = [](int j) { return ((j >> 7) * 64 + (j & 63)) * 2 + ((j >> 6) & 1); };
     for (int word = wave; word * 64 < N; word += 16) {
         const int j = word * 64 + lane;
+        const uint64_t key = donor_key(Hr, stride, NF, word, l0, n);
         if (j < N) {
-            const int s = find_slot(donor_key(Hr, stride, NF, word, lane, l0, n), tab, HS, cap,
-                                    &count, &extra);
+            const int s = find_slot(key, tab, HS, cap, &count, &extra);
             if (s >= 0) {
                 atomicMin(&first[s], j);
                 atomicAdd(&members[s], 1);

@@ -114,18 +114,6 @@ __device__ __forceinline__ void fma_in_place(double &v, double p, double q) {
     asm("v_fma_f64 %0, %1, %0, %2" : "+v"(v) : "v"(p), "v"(q));
 }
 
-// Register need of a class sweep: the donor words, four values per class word
-// and about 45 more; the kernels are compiled for the waves per SIMD it gives.
-__host__ __device__ constexpr int csweep_waves_per_simd(int nslot, int ks, int vgpr_per_slot) {
-    const int need = (nslot + 4 * ks) * vgpr_per_slot + (vgpr_per_slot == 2 ? 60 : 45);
-    const int w = 512 / ((need + 7) / 8 * 8);
-    return w > 8 ? 8 : (w < 1 ? 1 : w);
-}
-__host__ __device__ constexpr int csweep_max_waves(int nslot, int ks, int vgpr_per_slot) {
-    const int w = 4 * csweep_waves_per_simd(nslot, ks, vgpr_per_slot);
-    return w > 8 ? 8 : w;
-}
-
 template <class PT, int NSLOT, int KS, int DIR, bool MUV>
 __global__ void __launch_bounds__(64 * csweep_max_waves(NSLOT, KS, PT::vgpr_per_slot))
 __attribute__((amdgpu_waves_per_eu(csweep_waves_per_simd(NSLOT, KS, PT::vgpr_per_slot))))

@@ -47,13 +47,15 @@ def _model(ls, H, N, rho, mu):
 # N: the smallest with classes, the edges of donor words and id words, one
 # more wave than 160 donor words, and a group of several waves; L: one block,
 # one variant more, ragged last blocks, more than one launch of the sweep;
-# targets at the first and last variants of blocks and of the sequence
-@pytest.mark.parametrize("N,L,K,vec", [
-    (512, 65, 4, False), (513, 128, 4, True), (640, 200, 5, False), (703, 129, 6, False),
-    (1000, 2200, 12, True), (2049, 333, 20, False), (4160, 97, 60, False),
-    (10241, 150, 100, False), (21000, 80, 100, True)])
-def test_class_sweep_vs_oracle(ls, N, L, K, vec):
-    H, rho, mu = _case(N, L, K, seed=N + L, vec=vec)
+# targets at the first and last variants of blocks and of the sequence; many
+# classes: groups of seven waves, and FP64 on four waves and on the plain sweep
+@pytest.mark.parametrize("N,L,K,vec,switch", [
+    (512, 65, 4, False, 2e-3), (513, 128, 4, True, 2e-3), (640, 200, 5, False, 2e-3),
+    (703, 129, 6, False, 2e-3), (1000, 2200, 12, True, 2e-3), (2049, 333, 20, False, 2e-3),
+    (4160, 97, 60, False, 2e-3), (10241, 150, 100, False, 2e-3), (21000, 80, 100, True, 2e-3),
+    (9900, 100, 100, False, 1e-3), (50000, 70, 300, False, 1e-4), (5000, 100, 700, False, 2e-3)])
+def test_class_sweep_vs_oracle(ls, N, L, K, vec, switch):
+    H, rho, mu = _case(N, L, K, seed=N + L, switch=switch, vec=vec)
     rec = np.unique([0, 63, 64, N // 2, N - 65, N - 2, N - 1]).astype(np.int32)
     targets = sorted({0, 15, 16, 31, 32, 63, L - 2, L - 1})
     m = _model(ls, H, N, rho, mu)
@@ -106,6 +108,26 @@ def test_class_sweep_equals_plain_sweep(ls, prec):
                 assert (np.abs(a - b).max(axis=1) / b.sum(axis=1)).max() <= F32_POST_ATOL
             else:
                 check_reduced(prec, a, b, "log")
+
+
+def test_fp64_with_many_classes_is_plain(ls):
+    """Sixteen class words: FP32 takes the class sweep, FP64 the plain one (the
+    bits of a forced shape)."""
+    N, L = 5000, 100
+    H, rho, mu = _case(N, L, 700, seed=N + L)
+    m = _model(ls, H, N, rho, mu)
+    assert m.c.reserved >> 8 == 16
+    rec = np.array([0, 4999], np.int32)
+
+    def moved(prec):
+        t = ls.Table(m, 0, prec, rec)
+        ls.forward(t, m, L - 1)
+        return _np(t.state)
+
+    for prec, same in (("fp64", True), ("fp32", False)):
+        own = moved(prec)
+        with forced_shape(*ls.kernel_shape(N, prec)):
+            assert np.array_equal(own, moved(prec)) == same
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])

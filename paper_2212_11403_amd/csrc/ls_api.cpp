@@ -253,7 +253,9 @@ bool class_shape(int32_t N, int prec, int kw, int *nslot, int *nwaves) {
 // one. Measured / model (ns): N = 10,000 FP32 (B, kw) = (64, 6) 56 / 58,
 // (64, 12) 68 / 74, (32, 12) 119 / 111; FP64 (32, 4) 144 / 132, (32, 6) 207 /
 // 210, (64, 16) 468 / 443; N = 50,000 FP32 (32, 12) 720 / 801, (32, 16) 832 /
-// 914. Below N = 5,000 both sides are bound by the time of a step's chain and
+// 914. (The boundary was measured with P and Q in two LDS reads; as one pair
+// it takes 4 to 20% less, which leaves the choice on the plain sweep's side.)
+// Below N = 5,000 both sides are bound by the time of a step's chain and
 // come out low alike.
 double class_step_cost(int32_t N, int prec, int lb, int kw) {
     int ns = 0, nw = 0;

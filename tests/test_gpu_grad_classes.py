@@ -7,7 +7,8 @@ import numpy as np
 import pytest
 
 import oracle
-from lsinputs import MosaicSpec, mosaic_haplotypes, rho_from_spacings, spacings
+from lsinputs import (MosaicSpec, mosaic_haplotypes, pack_haplotypes, rho_from_spacings,
+                      spacings)
 
 from _gpu import F32_LOGLIK_RTOL, forced_shape, need_gpu
 
@@ -97,3 +98,20 @@ def test_class_gradient_repeats_and_agrees(ls, prec):
     # every recipient's term is at most 1 / rho and the sum has N of them; the
     # largest component bounds the scale from below
     assert (a["grad_rho"] - c["grad_rho"]).abs().max() <= tol * c["grad_rho"].abs().max()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_class_gradient_of_private_alleles(ls, prec):
+    """A recipient that mismatches every donor at a variant has mismatch mass
+    1 there: d log P / d mu^l = 1/mu to FP64's rounding, in FP32 too (its
+    matching classes add exactly 0)."""
+    N, L, mu = 700, 300, 1e-4
+    H, rho, _ = _case(N, L, 6, seed=4)
+    h = np.unpackbits(H.view(np.uint8).reshape(L, -1), axis=1, bitorder="little")[:, :N].copy()
+    at = np.array([0, 5, 63, 64, 130, 255, 256, 299])
+    h[at, :] = 0
+    h[at, 17] = 1
+    m = ls.Model(pack_haplotypes(h), N, rho, np.full(L, mu))
+    assert m.c.reserved != 0
+    g = ls.loglik_grad(m, recipients=np.array([17], np.int32), prec=prec)["grad_mu"].cpu().numpy()
+    assert np.abs(g[at] * mu - 1.0).max() <= 1e-14

@@ -37,9 +37,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 # Published MI355X vector peaks (dense, no sparsity): FP32 157.3 TFLOP/s,
-# FP64 78.6 TFLOP/s, an FMA counting as two flops.
+# an FMA counting as two flops.
 FP32_PEAK = 157.3e12
-FP64_PEAK = 78.6e12
 # Algorithmic flops per cell and direction: FMA (2) + MUL + ADD; the emission
 # select is not a flop.
 FLOPS_PER_CELL = 4
@@ -54,11 +53,20 @@ ISSUE_OPS_PER_CELL = 3
 HBM_PEAK = 8.0e12
 SWEEP_CHUNK = 2048  # variants per sweep launch (the library splits longer sweeps)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_bwd_fp32_c2_traffic.txt")
-SWEEP_SOURCES = ["ls_sweep.h", "ls_device.h", "ls_internal.h", "ls_sweep_f32_bwd.hip"]
+SWEEP_SOURCES = ["ls_csweep.h", "ls_class.h", "ls_device.h", "ls_internal.h"]
+# The class sweep (haplotypes grouped by their alleles over a block of B
+# variants): flops per class, recipient and variant (two masked multiplies, an
+# add, two FMAs) and per donor, recipient and block boundary (an FMA and the
+# add to the class's sum), and LDS bytes per donor at a boundary (the class's
+# FP32 pair, read, and its FP64 sum, read and written).
+CLASS_FLOPS_PER_CLASS = 7
+CLASS_FLOPS_PER_DONOR = 3
+CLASS_LDS_BYTES_PER_DONOR = 24
+LDS_PEAK = 256 * 128 * 2.4e9  # 256 CUs x 128 bytes per clock x 2.4 GHz
 
 
 def sweep_source_hash():
-    """SHA-1 over the sources of the FP32 backward sweep kernel."""
+    """SHA-1 over the sources of the FP32 class sweep kernel."""
     import hashlib
     h = hashlib.sha1()
     for name in SWEEP_SOURCES:
@@ -67,10 +75,10 @@ def sweep_source_hash():
     return h.hexdigest()
 
 
-def measured_traffic(shape):
-    """HBM bytes per launch of the backward sweep from the committed counter
-    summary, or None if it is absent or was taken on other kernel sources or
-    another kernel shape."""
+def measured_traffic(block, words):
+    """HBM bytes per launch of the backward class sweep from the committed
+    counter summary, or None if it is absent or was taken on other kernel
+    sources, block length or class words."""
     try:
         kv = {}
         with open(TRAFFIC_FILE) as f:
@@ -80,7 +88,7 @@ def measured_traffic(shape):
                     kv[k.strip()] = v.strip()
         if kv.get("kernel_source_sha1") != sweep_source_hash():
             return None
-        if kv.get("shape") != f"{shape[0]}x{shape[1]}":
+        if kv.get("class_block") != f"{block}x{words}":
             return None
         return float(kv["traffic_bytes_per_launch"])
     except (OSError, KeyError, ValueError):
@@ -471,19 +479,38 @@ def main():
     launches = -(-(L - 1) // SWEEP_CHUNK)
     launch_s = r32["bwd_ms"] / 1e3 / launches
     cells_launch = cells / launches
-    flops = FLOPS_PER_CELL * cells_launch / launch_s
-    lane_ops = ISSUE_OPS_PER_CELL * cells_launch / launch_s
-    rows_bytes = SWEEP_CHUNK * N / 8.0                 # one bit per donor and variant
     snap_bytes = T / launches * float(N) * N * 4       # beta snapshots, FP32
-    roofline = {"bound": "alu", "achieved": flops / 1e12, "peak": FP32_PEAK / 1e12,
-                "unit": "TFLOP/s", "frac": flops / FP32_PEAK,
-                "traffic": measured_traffic(shape),
-                "kernel": f"sweep_kernel<PrecF32,{shape[0]},1> (backward)",
-                "flops_per_cell": FLOPS_PER_CELL, "launches_per_sweep": launches,
-                "cells_per_launch": cells_launch, "launch_ms": launch_s * 1e3,
-                "algorithmic_bytes_per_launch": rows_bytes + snap_bytes,
-                "issue": {"achieved_lane_ops_per_s": lane_ops, "peak_lane_ops_per_s": ISSUE_PEAK,
-                          "frac": lane_ops / ISSUE_PEAK, "ops_per_cell": ISSUE_OPS_PER_CELL}}
+    common = {"launches_per_sweep": launches, "cells_per_launch": cells_launch,
+              "launch_ms": launch_s * 1e3}
+    if model.c.reserved:
+        # haplotype classes: blocks of `block` variants, `words` x 64 classes
+        block, words = 1 << (model.c.reserved & 255), model.c.reserved >> 8
+        steps = cells_launch / N                       # recipients x variants
+        lds = CLASS_LDS_BYTES_PER_DONOR * cells_launch / block / launch_s
+        flops = (CLASS_FLOPS_PER_CLASS * 64 * words * steps +
+                 CLASS_FLOPS_PER_DONOR * cells_launch / block) / launch_s
+        ids_bytes = SWEEP_CHUNK / block * N * 2.0      # class of every donor and block
+        roofline = {"bound": "lds", "achieved": lds / 1e12, "peak": LDS_PEAK / 1e12,
+                    "unit": "TB/s", "frac": lds / LDS_PEAK,
+                    "traffic": measured_traffic(block, words),
+                    "kernel": f"csweep_kernel<PrecF32,...,{words},1> (backward, blocks of "
+                              f"{block} variants)",
+                    "class_block": block, "class_words": words, **common,
+                    "algorithmic_bytes_per_launch": ids_bytes + snap_bytes,
+                    "alu": {"achieved": flops / 1e12, "peak": FP32_PEAK / 1e12,
+                            "unit": "TFLOP/s", "frac": flops / FP32_PEAK}}
+    else:
+        flops = FLOPS_PER_CELL * cells_launch / launch_s
+        lane_ops = ISSUE_OPS_PER_CELL * cells_launch / launch_s
+        rows_bytes = SWEEP_CHUNK * N / 8.0             # one bit per donor and variant
+        roofline = {"bound": "alu", "achieved": flops / 1e12, "peak": FP32_PEAK / 1e12,
+                    "unit": "TFLOP/s", "frac": flops / FP32_PEAK, "traffic": None,
+                    "kernel": f"sweep_kernel<PrecF32,{shape[0]},1> (backward)",
+                    "flops_per_cell": FLOPS_PER_CELL, **common,
+                    "algorithmic_bytes_per_launch": rows_bytes + snap_bytes,
+                    "issue": {"achieved_lane_ops_per_s": lane_ops,
+                              "peak_lane_ops_per_s": ISSUE_PEAK,
+                              "frac": lane_ops / ISSUE_PEAK, "ops_per_cell": ISSUE_OPS_PER_CELL}}
     line = {
         "metric": "LS fwd+bwd cell updates/s (N^2 L / s), FP32-scaled sweep",
         "value": value,
@@ -516,12 +543,10 @@ def main():
         r64 = timed("fp64", args.fp64_steps, 0)
         log(f"fp64: {r64['ms_per_step']:.1f} ms/step (bwd {r64['bwd_ms']:.1f}, fwd+post "
             f"{r64['fwd_ms']:.1f})")
-        f64_flops = FLOPS_PER_CELL * cells / (r64["bwd_ms"] / 1e3)
         line["fp64"] = {"value": cells / (r64["ms_per_step"] / 1e3), "ms_per_step":
                         r64["ms_per_step"], "backward_sweep_ms": r64["bwd_ms"],
                         "forward_sweep_and_posterior_ms": r64["fwd_ms"],
-                        "shape": list(ls.kernel_shape(N, "fp64")),
-                        "backward_flops_frac": f64_flops / FP64_PEAK}
+                        "shape": list(ls.kernel_shape(N, "fp64"))}
         ll32, ll64 = r32["loglik"], r64["loglik"]
         line["max_rel_loglik_err_fp32_vs_fp64"] = float(np.max(np.abs(ll32 - ll64) / np.abs(ll64)))
     if not args.no_fp64 and not args.no_accuracy:

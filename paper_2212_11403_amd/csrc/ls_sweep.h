@@ -510,36 +510,51 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     // at l = 0 gives c = 0, b = kappa / (N-1), i.e. alpha^0); backward
     // variant l uses rho_l. A decoding forward sweep has the emission
     // divisor in A and B (cnum, bmul), so its vector is kappa alpha^l.
-    // What is read ahead is the table pair (FP32) or rho (FP64), and A and B
-    // are formed from it when the step begins: formed at once, they would
-    // wait for the load.
+    // FP64 in single-wave groups: rho is read ahead and A and B are formed from
+    // it when the step begins; formed at once, they would wait for the load.
+    // Groups of several waves form them when they read it: there the late form
+    // took registers and time (ns per recipient step and compute unit, backward:
+    // 48 slots x 8 waves 991 -> 1,489, 48 x 2 242 -> 306; forward 100 x 8 2,120 ->
+    // 2,278).
+    constexpr bool LATE = ONE && sizeof(T) == 8;
     struct Coef {
         T x, y;
-    };
-    auto coef_read = [&](int l) __attribute__((always_inline)) -> Coef {
-        if constexpr (sizeof(T) == 4) return Coef{coef[2 * l], coef[2 * l + 1]};
-        else if constexpr (DIR == 0) return Coef{rho[l > 0 ? l - 1 : 0], (T)0};  // no branch: it costs registers
-        else return Coef{rho[l], (T)0};
     };
     // (held in vector registers: left to itself the compiler reads the kernel
     // arguments again at every step and waits for them)
     T cnum = (T)a.cnum, bmul = (T)a.bmul;
-    if constexpr (sizeof(T) == 8 && NSLOT <= 64) {
+    if constexpr (LATE && NSLOT <= 64) {
         cnum = in_vgpr(cnum);
         bmul = in_vgpr(bmul);
     }
-    auto coef_form = [&](int l, const Coef &q, T &A, T &B) __attribute__((always_inline)) {
+    auto coef_of = [&](int l, double r0, T &A, T &B) __attribute__((always_inline)) {
+        if constexpr (DIR == 0) {
+            const double rr = l > 0 ? r0 : 1.0;
+            const double keep = l > 0 ? 1.0 : 0.0;
+            A = keep * (1.0 - rr) * (LATE ? (double)cnum : a.cnum);
+            B = rr * (LATE ? (double)bmul : a.bmul);
+        } else {
+            A = (1.0 - r0) * (LATE ? (double)cnum : a.cnum);
+            B = r0 * (LATE ? (double)bmul : a.bmul);
+        }
+    };
+    auto coef_read = [&](int l) __attribute__((always_inline)) -> Coef {
         if constexpr (sizeof(T) == 4) {
+            return Coef{coef[2 * l], coef[2 * l + 1]};
+        } else {
+            const double r0 = rho[DIR == 1 ? l : l > 0 ? l - 1 : 0];  // no branch: it costs registers
+            if constexpr (LATE) return Coef{r0, (T)0};
+            Coef q;
+            coef_of(l, r0, q.x, q.y);
+            return q;
+        }
+    };
+    auto coef_form = [&](int l, const Coef &q, T &A, T &B) __attribute__((always_inline)) {
+        if constexpr (LATE) {
+            coef_of(l, q.x, A, B);
+        } else {
             A = q.x;
             B = q.y;
-        } else if constexpr (DIR == 0) {
-            const double rr = l > 0 ? q.x : 1.0;
-            const double keep = l > 0 ? 1.0 : 0.0;
-            A = keep * (1.0 - rr) * cnum;
-            B = rr * bmul;
-        } else {
-            A = (1.0 - q.x) * cnum;
-            B = q.x * bmul;
         }
     };
     auto coefs_at = [&](int l, T &A, T &B) __attribute__((always_inline)) {

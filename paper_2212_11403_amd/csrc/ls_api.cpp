@@ -203,9 +203,11 @@ bool choose_shape(int32_t N, int prec, Shape *out, bool grad = false, bool prior
 }
 
 // ---- class sweeps -------------------------------------------------------------
-// ls_model.reserved: 0 (no classes) or log2 of the block length + 256 times
-// the class words of a row.
-int class_lb(const ls_model *m) { return m->reserved & 255; }
+// ls_model.reserved: 0 (no classes) or log2 of the block length (4 to 6) + 256
+// times the class words of a row, and a bit for each precision whose range the
+// model leaves (share_fall).
+constexpr int32_t kPlainF32 = 8, kPlainF64 = 16;
+int class_lb(const ls_model *m) { return m->reserved & 7; }
 int class_words(const ls_model *m) { return (m->reserved >> 8) & 255; }
 
 int class_groups(int nslot, int nwaves, int kw, int vps) {
@@ -310,11 +312,50 @@ constexpr int kClassMinMove = 64;
 bool class_route(const ls_model *m, int prec, int variants) {
     if (class_lb(m) == 0 || m->prior || variants < kClassMinMove) return false;
     if (prec != LS_FP32 && prec != LS_FP64) return false;
+    if (m->reserved & (prec == LS_FP64 ? kPlainF64 : kPlainF32)) return false;
     // (the block length is chosen for FP32)
     if (prec == LS_FP64 && class_step_cost(m->N, prec, class_lb(m), class_words(m)) >=
                                0.85 * plain_step_cost(m->N, prec))
         return false;
     return std::getenv("LS_FORCE_SHAPE") == nullptr;  // a forced shape is a plain sweep's
+}
+
+// Bits by which a donor's share of the column sum may fall in either direction,
+// plus one emission. At a mismatch a share falls by mu / (1 - mu); the jump into
+// a variant lifts it to at least rho / (N - 1), times at most one emission. So
+// only runs of (near) zero rho take it far down. Inside a block P of a class
+// grows to 2 / A_k, the inverse of its share, and a class that had all but
+// vanished may become the best one again: the class sweeps have the range for
+// it up to the limits below, the plain sweep, which renormalises every value
+// at every variant, up to the type's own. In logarithms rounded up: the model's
+// smallest rho and mu first, which settles it for real maps, else variant by
+// variant.
+constexpr double kFallF32 = 90.0;   // P and A within 2^+-90 (csweep_kernel's clamp: 2^100)
+constexpr double kFallF64 = 480.0;  // and the gradient's a z, in double, within 2^-960
+double share_fall(int32_t N, int32_t L, const std::vector<double> &rho, double mu,
+                  const std::vector<double> &muv) {
+    auto bits = [](double x) { return x > 0.0 ? (double)-std::ilogb(x) : 1e9; };
+    const double n = std::log2((double)(N - 1));
+    double mu_min = muv.empty() ? mu : 1.0, rho_min = 1.0;
+    for (double x : muv) mu_min = std::min(mu_min, x);
+    for (double x : rho) rho_min = std::min(rho_min, x);
+    const double quick = n + bits(rho_min) + 2.0 * bits(mu_min);
+    if (quick <= kFallF32) return quick;
+    auto em = [&](int32_t l) { return bits(muv.empty() ? mu : muv[(size_t)l]); };
+    double most = 0.0;
+    for (int dir = 0; dir < 2; ++dir) {
+        double d = n;
+        for (int32_t k = 0; k < L; ++k) {
+            const int32_t l = dir == 0 ? k : L - 1 - k;
+            if (k > 0) {  // a donor that does not jump keeps 1 - rho (rho <= 0.9)
+                const double r = rho[(size_t)(dir == 0 ? l - 1 : l)];
+                d = std::min(d + 3.7 * r, n + bits(r));
+            }
+            d += em(l);
+            most = std::max(most, d + em(l));
+        }
+    }
+    return most;
 }
 
 void class_ptrs(const ls_model *m, int prec, lsk::ClassPtrs &c) {
@@ -604,9 +645,10 @@ ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *str
             reinterpret_cast<double *>(eb + 2 * L * (sizeof(double) + sizeof(float))), st);
         if (e != hipSuccess) return LS_ERR_DEVICE;
     }
-    // haplotype classes: the class sweep keeps its values in range with
-    // powers of two taken out once a step, which covers these parameters
-    // (a jump factor of at most 10 and an emission ratio of at least 2^-30)
+    // haplotype classes: the class sweep keeps its sums in range with powers
+    // of two taken out once a step, which covers these parameters (a jump
+    // factor of at most 10 and an emission ratio of at least 2^-30), and the
+    // classes' values as far as share_fall's limits
     int32_t classes = 0;
     bool in_range = lsk::class_section(m->N, m->L) && ws_bytes >= ls_model_workspace_bytes(m->N, m->L) &&
                     !m->prior;
@@ -614,6 +656,12 @@ ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *str
     if (in_range && !m->mu_vec) in_range = mu_fits(m->mu);
     for (size_t k = 0; in_range && k < muv.size(); ++k) in_range = mu_fits(muv[k]);
     for (size_t k = 0; in_range && k < rho.size(); ++k) in_range = rho[k] <= 0.9;
+    int32_t plain = 0;
+    if (in_range) {
+        const double fall = share_fall(m->N, m->L, rho, m->mu, muv);
+        plain = (fall > kFallF32 ? kPlainF32 : 0) | (fall > kFallF64 ? kPlainF64 : 0);
+        in_range = plain != (kPlainF32 | kPlainF64);
+    }
     // (and past N = 81,920 no class sweep holds the donors in registers)
     int ns = 0, nw = 0;
     if (in_range && class_shape(m->N, LS_FP32, 2, &ns, &nw)) {
@@ -640,7 +688,7 @@ ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *str
     m->Hr = Hr;
     m->hr_stride = hs;
     m->nf = m->N / 64;
-    m->reserved = classes;
+    m->reserved = classes ? classes | plain : 0;
     return LS_OK;
 }
 

@@ -158,9 +158,11 @@ csweep_kernel(const uint32_t *__restrict__ ids, const uint64_t *__restrict__ key
     const T v_fresh = DIR == 0 ? (T)0 : (T)1;
     const int B = 1 << lb;
     const int idw = ((N + 127) >> 7) * 64;  // id words of a block
-    // S is kept in [2^-LIM, 2^LIM]; while it falls, P of a class without mass
-    // and Q of one without members (the recipient's own) may grow: both are
-    // held finite, as they meet the factors A = 0 and n = 0
+    // S is kept in [2^-LIM, 2^LIM], so P <= 2 / A after a renormalisation: below
+    // 2^91 in FP32, as no donor's share falls below 2^-90 (the model's check,
+    // share_fall). The clamp is for the class of the recipient alone, which
+    // has no mass and no members: its P and Q grow while S falls, and are held
+    // finite, as they meet the factors A = 0 and n = 0
     constexpr int LIM = sizeof(T) == 4 ? 24 : 64;
     const T big = pow2((T)0, sizeof(T) == 4 ? 100 : 900);
 

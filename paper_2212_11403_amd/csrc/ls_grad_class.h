@@ -188,7 +188,12 @@ grad_class_kernel(const uint32_t *__restrict__ ids, const uint64_t *__restrict__
         if (wave == 0) {
             const int l0 = m << a.lb;
             const int nv = min(B, L - l0);
+            // X and Y of a class are held times 2^-eY, eY the exponent of Y, and its P'
+            // and Q' Y term accordingly with P' 2^eY: the same products, but a class
+            // whose a and z are both small keeps its X in range (X alone has the square
+            // of the smallest share)
             T A[KS], X[KS], Y[KS], n[KS];
+            int eY[KS];
             uint64_t mis[KS];  // bit b: the class mismatches the recipient at variant l0 + b
             const uint32_t idp = ids[(int64_t)m * idw + (i >> 7) * 64 + (i & 63)];
             const int ci = uniform((int)((i & 64 ? idp >> 16 : idp & 0xffffu) / 4u) - 1);
@@ -203,8 +208,10 @@ grad_class_kernel(const uint32_t *__restrict__ ids, const uint64_t *__restrict__
                     xy += sums[w * 3 * E + 2 * E + k + 1];
                 }
                 A[s] = (T)xa;
-                X[s] = (T)xx;
-                Y[s] = (T)xy;
+                eY[s] = xy > 0.0 ? exponent_of(xy) : 0;
+                const double down = pow2(0.0, -eY[s]);
+                X[s] = (T)(xx * down);
+                Y[s] = (T)(xy * down);
                 n[s] = (T)cnt[(int64_t)m * CK + k] - (k == ci ? (T)1 : (T)0);
                 mis[s] = keys[(int64_t)m * CK + k] ^ own_key;
             }
@@ -290,9 +297,9 @@ grad_class_kernel(const uint32_t *__restrict__ ids, const uint64_t *__restrict__
                 T y = (T)0;
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
-                    Pb[s] = (T)1;
+                    Pb[s] = pow2((T)0, eY[s]);
                     Qb[s] = (T)0;
-                    y += Y[s];
+                    y += Y[s] * Pb[s];
                 }
                 Sb = wave_sum(y);
             }
@@ -410,7 +417,7 @@ grad_class_kernel(const uint32_t *__restrict__ ids, const uint64_t *__restrict__
             if (lane == 0) lp[0] = lq[0] = (T)0;
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                lp[s * 64 + lane + 1] = Pb[s] * f;
+                lp[s * 64 + lane + 1] = Pb[s] * f * pow2((T)0, -eY[s]);
                 lq[s * 64 + lane + 1] = Qb[s] * f;
             }
         }

@@ -52,6 +52,8 @@ def _rho(kind):
         rho[2:180] = 0.0
     elif kind == "tiny":        # a share still falls no lower than 2^-76 at mu = 1e-4
         rho[:] = 2.0 ** -52
+    elif kind == "least":       # the same at mu = 0.11 (and too little at 1e-4)
+        rho[:] = 2.0 ** -72
     elif kind == "tiniest":
         rho[:] = 1e-300
     return rho
@@ -93,8 +95,8 @@ def test_sweeps(ls, kind, mu, a, b):
 
 # half 0 falls up to both ends of a block in which half 1 falls further: both
 # vectors of half 0 are small at that block's ends and their product smaller
-@pytest.mark.parametrize("kind", ["zero", "run", "tiny", "tiniest"])
-@pytest.mark.parametrize("mu,a,b", [(1e-4, 6, 13), (1e-3, 2, 5), (1e-6, 3, 7)])
+@pytest.mark.parametrize("kind", ["zero", "run", "tiny", "least", "tiniest"])
+@pytest.mark.parametrize("mu,a,b", [(1e-4, 6, 13), (1e-3, 2, 5), (1e-6, 3, 7), (0.11, 22, 63)])
 def test_gradient(ls, kind, mu, a, b):
     H, rho = _haplotypes([(0, 65 - 2 * a, a), (1, 65, b), (0, 128, a)]), _rho(kind)
     assert _takes_classes(ls, H)

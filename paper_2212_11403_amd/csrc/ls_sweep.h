@@ -131,6 +131,16 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     // kappa, inside half's range, whatever the prior)
     constexpr bool SNORM = QH && PI && DIR == 1;
     static_assert(!QH || XMUL, "FP16-stored sweeps use the masked emission");
+    // single-wave groups in FP32 arithmetic that have a several-wave form (NP
+    // waves of SL slots, run_shape) add the column as it does: NP partial sums
+    // (of 20 and 28 slots: the last of its slots hold no donor and add 0)
+    constexpr bool kSplit = ONE && sizeof(T) == 4 && !EVERY && !PI && split_slots(NSLOT) > 0;
+    constexpr int SL = kSplit ? split_slots(NSLOT) : NSLOT, NP = kSplit ? split_waves(NSLOT) : 1;
+    // FP16-stored backward of either form: every slot's c v + b is rounded to
+    // half in one step (one instruction), so the lanes without a donor are
+    // masked after it; a multiply in between would round special slots twice
+    constexpr bool KEEP_LAST =
+        QH && DIR == 1 && !PI && (kSplit || (!ONE && (NSLOT == 4 || NSLOT == 8)));
     __shared__ T red[2 * kRedStride];
 
     const int nwaves = uniform(blockDim.x >> 6);
@@ -209,15 +219,21 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     T S;                // sum of the resident vector
     T part_w = (T)0;    // SNORM: this lane's pi'-weighted partial sum
     T Wsum = (T)0;      // SNORM: the pi'-weighted column sum W'
+    // this lane's partial sums of the column
+    struct Part {
+        T x[NP];
+    };
     // the workgroup sum of a step's partials (with SNORM also W')
-    auto reduce = [&](T part) __attribute__((always_inline)) -> T {
+    auto reduce = [&](const Part &part) __attribute__((always_inline)) -> T {
         if constexpr (SNORM) {
-            T x[4] = {part, part_w, (T)0, (T)0};
+            T x[4] = {part.x[0], part_w, (T)0, (T)0};
             block_sum4<MAXW>(x, red, parity, wave);
             Wsum = x[1];
             return x[0];
+        } else if constexpr (kSplit) {
+            return waves_sum<NP>(part.x);
         } else {
-            return block_sum<MAXW>(part, red, parity, wave, nwaves);
+            return block_sum<MAXW>(part.x[0], red, parity, wave, nwaves);
         }
     };
 
@@ -253,11 +269,29 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     // Lane partial sums of the column: even slots into acc0, odd into acc1,
     // starting from slots 0 and 1 (the entries are never -0, so this equals
     // adding them to zero).
-    auto accumulate = [&](int s, T x, T &acc0, T &acc1) __attribute__((always_inline)) {
+    struct Acc {
+        T a[NP], b[NP];
+    };
+    auto accumulate = [&](int s, T x, Acc &acc) __attribute__((always_inline)) {
+        // (kSplit: a wave's regular slots come four at a time, then its special
+        // ones, as the words are handed out)
+        const int q = kSplit ? s / 4 % NP : 0;
+        T &acc0 = acc.a[q], &acc1 = acc.b[q];
+        if constexpr (kSplit) s = s / 4 / NP * 4 + s % 4;
         if (s == 0) acc0 = x;
         else if (s == 1) acc1 = x;
         else if (s & 1) acc1 += x;
         else acc0 += x;
+    };
+    auto acc_start = [&](Acc &acc) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) acc.b[q] = (T)0;
+    };
+    auto acc_parts = [&](const Acc &acc) __attribute__((always_inline)) -> Part {
+        Part p;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) p.x[q] = acc.a[q] + acc.b[q];
+        return p;
     };
     // the column sum a step hands on: the backward with a prior matrix sums
     // pi' v (its normaliser W'), every other sweep v itself; the FP16-stored
@@ -270,14 +304,14 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         else if (s & 1) acc1 = fma(pv[s], x, acc1);
         else acc0 = fma(pv[s], x, acc0);
     };
-    auto account_sum = [&](int s, T x, T &acc0, T &acc1) __attribute__((always_inline)) {
+    auto account_sum = [&](int s, T x, Acc &acc) __attribute__((always_inline)) {
         if constexpr (SNORM) {
-            accumulate(s, x, acc0, acc1);
+            accumulate(s, x, acc);
             weighted(s, x, aw0, aw1);
         } else if constexpr (PI && DIR == 1) {
-            weighted(s, x, acc0, acc1);
+            weighted(s, x, acc.a[0], acc.b[0]);
         } else {
-            accumulate(s, x, acc0, acc1);
+            accumulate(s, x, acc);
         }
     };
     // FP16 storage: each new vector is rounded to half at every step, so the
@@ -301,10 +335,12 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         return (s < NR) ? row[reg_base + s] : row[spec_off[s - NR]];
     };
     // Narrow single-wave groups read the row words one variant ahead, beside
-    // the coefficients (8 slots: 16 scalar registers). In a group of several
+    // the coefficients (8 slots: 16 scalar registers; FP64, whose steps are
+    // longer, also 12: in FP32 the copies cost more there than the wait, N = 640
+    // all recipients 0.46 us per variant against 0.42). In a group of several
     // waves the wait for the exchange through LDS waits for scalar loads too,
     // so the loads gain nothing there and the copies cost 5 to 10%.
-    constexpr bool AHEAD = ONE && NSLOT <= 12;
+    constexpr bool AHEAD = ONE && NSLOT <= (sizeof(T) == 8 ? 12 : 8);
     struct Words {
         uint64_t w[AHEAD ? NSLOT : 1];
     };
@@ -349,14 +385,15 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         flip = uniform((int)(rb != on_match)) ? ~0ull : 0ull;
     };
     auto xmul_all = [&](auto mask, uint64_t flip, T r) __attribute__((always_inline)) {
-        masked_scale_all<NSLOT>(v, mask, flip, r);
+        masked_scale_all<NSLOT, ONE>(v, mask, flip, r);
     };
-    // v <- theta^l (.) (c v + b); returns this lane's partial sum
+    // v <- theta^l (.) (c v + b); returns this lane's partial sums
     auto step = [&](int l, uint64_t sw_bits, T em, T ex, T c, T b_s, const Words &wx)
-                    __attribute__((always_inline)) -> T {
+                    __attribute__((always_inline)) -> Part {
         const uint64_t *row = Hr + (int64_t)l * a.hr_stride;
         const T b = in_vgpr(b_s);
-        T acc0, acc1 = (T)0;
+        Acc acc;
+        acc_start(acc);
         if constexpr (XMUL) {
             T r;
             uint64_t flip;
@@ -365,6 +402,8 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             for (int s = 0; s < NSLOT; ++s) {
                 if constexpr (PI && DIR == 0) {
                     v[s] = fma(c, (T)v[s], b * pv[s]);
+                } else if constexpr (KEEP_LAST) {
+                    v[s] = fma(c, (T)v[s], b);
                 } else if constexpr (DIR == 1) {
                     v[s] = keep_lanes(s, fma(c, (T)v[s], b));
                 } else {
@@ -378,13 +417,17 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             // FP16 storage rounds what a table holds: the backward vector
             // kappa beta^l before its emission, the forward kappa alpha^l
             if constexpr (DIR == 1) quantise();
+            if constexpr (KEEP_LAST) {
+#pragma unroll
+                for (int s = 0; s < NSLOT; ++s) v[s] = keep_lanes(s, v[s]);
+            }
             xmul_all([&](int s) __attribute__((always_inline)) { return step_mask(row, wx, s); },
                      flip, r);
             if constexpr (DIR == 0) quantise();
 #pragma unroll
-            for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc0, acc1);
+            for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc);
             if constexpr (SNORM) part_w = aw0 + aw1;
-            return acc0 + acc1;
+            return acc_parts(acc);
         }
         T ta, tb;
         thetas(sw_bits, em, ex, ta, tb);
@@ -396,31 +439,35 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             else bb = (s < NR) ? (s == 0 ? b * keep0 : b) : b * spec_keep[s - NR];
             const T nv = th * fma(c, (T)v[s], bb);
             v[s] = nv;
-            account_sum(s, nv, acc0, acc1);
+            account_sum(s, nv, acc);
         }
-        return acc0 + acc1;
+        return acc_parts(acc);
     };
     // v <- c v + b (no emission): the backward vector before theta^l
     auto affine = [&](T c, T b) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < NSLOT; ++s) v[s] = keep_lanes(s, fma(c, v[s], b));
+        for (int s = 0; s < NSLOT; ++s) {
+            if constexpr (KEEP_LAST) v[s] = keep_lanes(s, (T)(ST)fma(c, v[s], b));
+            else v[s] = keep_lanes(s, fma(c, v[s], b));
+        }
         quantise();
     };
-    // v <- theta^l (.) v; returns this lane's partial sum
-    auto emit = [&](int l) __attribute__((always_inline)) -> T {
+    // v <- theta^l (.) v; returns this lane's partial sums
+    auto emit = [&](int l) __attribute__((always_inline)) -> Part {
         const uint64_t *row = Hr + (int64_t)l * a.hr_stride;
         T em, ex, ta, tb;
         emis_at(l, em, ex);
-        T acc0, acc1 = (T)0;
+        Acc acc;
+        acc_start(acc);
         if constexpr (XMUL) {
             T r;
             uint64_t flip;
             xmul_params(row[self_off], em, ex, r, flip);
             xmul_all([&](int s) __attribute__((always_inline)) { return mask_of(row, s); }, flip, r);
 #pragma unroll
-            for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc0, acc1);
+            for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc);
             if constexpr (SNORM) part_w = aw0 + aw1;
-            return acc0 + acc1;
+            return acc_parts(acc);
         }
         thetas(row[self_off], em, ex, ta, tb);
 #pragma unroll
@@ -428,9 +475,9 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             const T th = lane_bit(mask_of(row, s)) ? tb : ta;
             const T nv = th * v[s];
             v[s] = nv;
-            account_sum(s, nv, acc0, acc1);
+            account_sum(s, nv, acc);
         }
-        return acc0 + acc1;
+        return acc_parts(acc);
     };
     // write v (times `scale`, as type D) to a row of N elements starting at
     // `dst`; the diagonal entry is written as 0 and lanes past N are skipped
@@ -604,10 +651,11 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             l = 0;
         } else {
             l = a.l0 + 1;
-            T acc0, acc1 = (T)0;  // same order as in step()
+            Acc acc;  // same order as in step()
+            acc_start(acc);
 #pragma unroll
-            for (int s = 0; s < NSLOT; ++s) accumulate(s, v[s], acc0, acc1);
-            S = block_sum<MAXW>(acc0 + acc1, red, parity, wave, nwaves);
+            for (int s = 0; s < NSLOT; ++s) accumulate(s, v[s], acc);
+            S = reduce(acc_parts(acc));
         }
         // the coefficients and the recipient's own word are read one variant
         // ahead, so their latency overlaps the previous step, and c of the
@@ -661,9 +709,9 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 w_nx = self_word(ln);
                 x_nx = words_at(ln);
                 const T c = coef_c(A, S);
-                T part = step(l, wb, em, ex, c, B, wx);
+                Part part = step(l, wb, em, ex, c, B, wx);
                 buf_store((IO)c, rs_c, c_voff, (l - a.l0 - 1) * a.R * (int)sizeof(IO));
-                S = block_sum<MAXW>(part, red, parity, wave, nwaves);
+                S = reduce(part);
                 account(S);
                 // alpha^l (exactly 0 on the recipient's lane and on lanes
                 // without a donor), unscaled: kappa = 1 in this mode. Only
@@ -717,8 +765,8 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 // -> 18.0 ms per 2,048 variants with c formed after the
                 // reduction instead)
                 const T c = coef_c(A, S);
-                T part = step(l, wb, em, ex, c, b, wx);
-                S = block_sum<MAXW>(part, red, parity, wave, nwaves);
+                Part part = step(l, wb, em, ex, c, b, wx);
+                S = reduce(part);
                 account(S);
             }
             if (kt < a.nt) snapshot();
@@ -732,7 +780,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         if (a.t < lstart) {
             // each column sum enters the log scale right after its
             // reduction (off the path to the next step's coefficients)
-            T part = emit(lstart);
+            Part part = emit(lstart);
             S = reduce(part);
             account(S);
             int l = lstart - 1;

@@ -585,15 +585,16 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             B = r0 * (LATE ? (double)bmul : a.bmul);
         }
     };
-    auto coef_read = [&](int l) __attribute__((always_inline)) -> Coef {
+    // (filled in place: returned by value, the FP64 backward of several waves
+    // multiplied its log scale inside the division chain, 1% of a step)
+    auto coef_read = [&](int l, Coef &q) __attribute__((always_inline)) {
         if constexpr (sizeof(T) == 4) {
-            return Coef{coef[2 * l], coef[2 * l + 1]};
+            q.x = coef[2 * l];
+            q.y = coef[2 * l + 1];
         } else {
             const double r0 = rho[DIR == 1 ? l : l > 0 ? l - 1 : 0];  // no branch: it costs registers
-            if constexpr (LATE) return Coef{r0, (T)0};
-            Coef q;
-            coef_of(l, r0, q.x, q.y);
-            return q;
+            if constexpr (LATE) q.x = r0;
+            else coef_of(l, r0, q.x, q.y);
         }
     };
     auto coef_form = [&](int l, const Coef &q, T &A, T &B) __attribute__((always_inline)) {
@@ -605,7 +606,9 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         }
     };
     auto coefs_at = [&](int l, T &A, T &B) __attribute__((always_inline)) {
-        coef_form(l, coef_read(l), A, B);
+        Coef q;
+        coef_read(l, q);
+        coef_form(l, q, A, B);
     };
     // c = A / S in the sweep precision. FP64 divides (correctly rounded).
     // FP32 refines the hardware reciprocal (about 1 ulp, and its error has a
@@ -693,7 +696,8 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 }
             }
             T em_nx, ex_nx;
-            Coef q_nx = coef_read(l <= lmax ? l : lmax);
+            Coef q_nx;
+            coef_read(l <= lmax ? l : lmax, q_nx);
             emis_at(l <= lmax ? l : lmax, em_nx, ex_nx);
             uint64_t w_nx = self_word(l <= lmax ? l : lmax);
             Words x_nx = words_at(l <= lmax ? l : lmax);
@@ -704,7 +708,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 const uint64_t wb = w_nx;
                 const Words wx = x_nx;
                 const int ln = l < lmax ? l + 1 : lmax;
-                q_nx = coef_read(ln);
+                coef_read(ln, q_nx);
                 emis_at(ln, em_nx, ex_nx);
                 w_nx = self_word(ln);
                 x_nx = words_at(ln);
@@ -743,7 +747,8 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         } else for (;;) {
             const int lend = kt < a.nt ? a.tgt_l[kt] : a.t;
             T em_nx, ex_nx;
-            Coef q_nx = coef_read(l <= lmax ? l : lmax);
+            Coef q_nx;
+            coef_read(l <= lmax ? l : lmax, q_nx);
             emis_at(l <= lmax ? l : lmax, em_nx, ex_nx);
             uint64_t w_nx = self_word(l <= lmax ? l : lmax);
             Words x_nx = words_at(l <= lmax ? l : lmax);
@@ -754,7 +759,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 const uint64_t wb = w_nx;
                 const Words wx = x_nx;
                 const int ln = l < lmax ? l + 1 : lmax;
-                q_nx = coef_read(ln);
+                coef_read(ln, q_nx);
                 emis_at(ln, em_nx, ex_nx);
                 w_nx = self_word(ln);
                 x_nx = words_at(ln);
@@ -789,7 +794,8 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 // the coefficients and the recipient's own word are read one
                 // variant ahead
                 T em_nx, ex_nx;
-                Coef q_nx = coef_read(l);
+                Coef q_nx;
+                coef_read(l, q_nx);
                 emis_at(l, em_nx, ex_nx);
                 uint64_t w_nx = self_word(l);
                 Words x_nx = words_at(l);
@@ -800,7 +806,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                     const uint64_t wb = w_nx;
                     const Words wx = x_nx;
                     const int ln = l > 0 ? l - 1 : 0;
-                    q_nx = coef_read(ln);
+                    coef_read(ln, q_nx);
                     emis_at(ln, em_nx, ex_nx);
                     w_nx = self_word(ln);
                     x_nx = words_at(ln);

@@ -242,26 +242,34 @@ hipError_t launch_posterior_rows(const void *alpha, int alpha_half, const void *
     if (R <= 0 || T <= 0) return hipSuccess;
     if (T > 65535) return hipErrorInvalidValue;
     const dim3 grid((unsigned)R, (unsigned)T), block(256);
-    // rows that fit the register kernel: full-precision inputs and at most 32
-    // values per thread (16 where they are read one at a time); 16-byte
-    // accesses need N and the strides to be multiples of the vector and every
-    // array to start on 16 bytes
+    // rows that fit the register kernel: full-precision inputs and at most 8
+    // accesses of 16 bytes a thread (32 FP32 values or 16 FP64) or 16 of one
+    // element; 16-byte accesses need N and the strides to be multiples of the
+    // vector and every array to start on 16 bytes
     auto aligned = [](const void *x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
     const int w = is_f64 ? 2 : 4;
     const bool vec = N % w == 0 && ts % w == 0 && rs % w == 0 && aligned(alpha) && aligned(beta) &&
                      aligned(P) && aligned(E);
     const int per = vec ? (N + 1024 * w - 1) / (1024 * w) : (N + 1023) / 1024;  // accesses a thread
-    if (!alpha_half && !beta_half && per <= (vec ? 8 : 16)) {
+    // single elements up to N = 1,024: two passes of 256 threads, as most of the
+    // 1,024 would hold nothing (us, P and E of N rows: FP64 N = 777 7.4 against
+    // 8.1, FP32 4.3 against 5.0; N = 1,501 17.0 against 14.8, 8.1 against 7.5)
+    if (!alpha_half && !beta_half && per <= (vec ? 8 : 16) && (vec || N > 1024)) {
         auto go = [&](auto kern, auto x) {
             using T_ = decltype(x);
             hipLaunchKernelGGL(kern, grid, dim3(1024), 0, st, (const T_ *)alpha, (const T_ *)beta,
                                recips, R, ts, rs, N, (T_ *)P, (T_ *)E);
         };
+        // (values held for rows longer than this one cost time: FP64 N = 2,001
+        // with 4, 8 and 16 a thread 22.8, 27.7 and 33.8 us)
         if (is_f64) {
-            if (!vec) go(&posterior_rows_reg_kernel<double, 16, 1>, 0.0);
-            else go(&posterior_rows_reg_kernel<double, 8, 2>, 0.0);
+            if (vec) go(&posterior_rows_reg_kernel<double, 8, 2>, 0.0);
+            else if (per <= 4) go(&posterior_rows_reg_kernel<double, 4, 1>, 0.0);
+            else if (per <= 8) go(&posterior_rows_reg_kernel<double, 8, 1>, 0.0);
+            else go(&posterior_rows_reg_kernel<double, 16, 1>, 0.0);
         } else {
-            if (!vec && per <= 8) go(&posterior_rows_reg_kernel<float, 8, 1>, 0.0f);
+            if (!vec && per <= 4) go(&posterior_rows_reg_kernel<float, 4, 1>, 0.0f);
+            else if (!vec && per <= 8) go(&posterior_rows_reg_kernel<float, 8, 1>, 0.0f);
             else if (!vec) go(&posterior_rows_reg_kernel<float, 16, 1>, 0.0f);
             else if (per <= 4) go(&posterior_rows_reg_kernel<float, 4, 4>, 0.0f);
             else go(&posterior_rows_reg_kernel<float, 8, 4>, 0.0f);

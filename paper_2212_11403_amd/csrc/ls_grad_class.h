@@ -80,6 +80,15 @@ __device__ __forceinline__ double read_lane(double x, int l) {
                             __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 
+// Between two uses of the same local memory by one wave: its lanes' accesses on
+// either side stay in order. The hardware keeps the order of a wave's own
+// accesses; the compiler, to which the two uses are arrays of different types
+// or different elements, need not.
+__device__ __forceinline__ void reuse_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <class PT, int NSLOT, int KS, bool MUV>
 __global__ void __launch_bounds__(64 * kGradClassMaxWaves)
 __attribute__((amdgpu_waves_per_eu(grad_class_waves_per_simd(NSLOT, KS, PT::vgpr_per_slot))))
@@ -215,6 +224,7 @@ grad_class_kernel(const uint32_t *__restrict__ ids, const uint64_t *__restrict__
                 n[s] = (T)cnt[(int64_t)m * CK + k] - (k == ci ? (T)1 : (T)0);
                 mis[s] = keys[(int64_t)m * CK + k] ^ own_key;
             }
+            reuse_lds();  // the sums are read; `kept` takes their place
             auto r_at = [&](int l) __attribute__((always_inline)) -> T {
                 if constexpr (!MUV) return (T)a.th_mis;
                 else if constexpr (sizeof(T) == 4) return rt[2 * l + 1];
@@ -412,6 +422,7 @@ grad_class_kernel(const uint32_t *__restrict__ ids, const uint64_t *__restrict__
                     gm += M * a.inv_mu - M1 * a.inv_omu;
                 }
             }
+            reuse_lds();  // `kept` is read; P' and Q' take its place
             // (P', Q') for the next z, in units in which its sum is near 1
             const T f = pow2((T)0, -exponent_of(Sb));
             if (lane == 0) lp[0] = lq[0] = (T)0;

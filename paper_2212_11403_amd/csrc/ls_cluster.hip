@@ -499,9 +499,11 @@ hipError_t launch_linkage_t(T *D, int32_t N, int32_t T_, double *Z, int32_t *ord
     const size_t lds = linkage_lds_bytes(N, sizeof(T));
     const size_t fixed = 10 * 16 * sizeof(WaveBest<T>) + 64;
     if (lds + fixed <= max_group_lds() && N <= kLinkageLdsMaxN) {
+        // the kernel's limit is one value of the process: set to all there is, so
+        // that threads clustering different N do not lower it for each other
         hipError_t e = hipFuncSetAttribute(
             reinterpret_cast<const void *>(&linkage_kernel<T, true>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(max_group_lds() - fixed));
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((linkage_kernel<T, true>), dim3(T_), dim3(threads), lds, st, D, N,
                            stride, w, Z, order);

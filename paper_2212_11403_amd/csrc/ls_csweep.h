@@ -501,11 +501,16 @@ hipError_t launch_csweep_one(const SweepPtrs &p, const ClassPtrs &c, const Sweep
     if (c.nwaves < 1 || c.nwaves > csweep_max_waves(NSLOT, KS, PT::vgpr_per_slot) ||
         (int64_t)c.nwaves * NSLOT * 64 < a.N || a.nblk < 1 || a.r0 < 0 || a.r0 + a.nblk > a.R)
         return hipErrorInvalidValue;
-    const size_t lds = (size_t)(64 * KS + 64) * (2 * sizeof(T) + c.nwaves * sizeof(double));
+    // the kernel's limit is set to what its widest group takes, whatever this one
+    // takes: it is one value of the process, and another thread may be about to
+    // launch the same kernel with more waves
+    auto bytes = [](int waves) { return (size_t)(64 * KS + 64) * (2 * sizeof(T) + waves * sizeof(double)); };
+    const size_t lds = bytes(c.nwaves);
     auto go = [&](auto kern) {
         if (lds > 65536) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            hipError_t e = hipFuncSetAttribute(
+                reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                (int)bytes(csweep_max_waves(NSLOT, KS, PT::vgpr_per_slot)));
             if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL(kern, dim3(a.nblk), dim3(64 * c.nwaves), lds, st, c.ids, c.keys, c.cnt,

@@ -126,7 +126,7 @@ void plan_grad_class(GradArgs &ga, int prec) {
 #undef LS_MATCH
     }
     const size_t es = prec == 0 ? 8 : 4;
-    if (!nslot || grad_class_lds(ks, ga.cls.lb, nwaves, es) > 128 * 1024) return;
+    if (!nslot || grad_class_lds(ks, ga.cls.lb, nwaves, es) > kGradClassMaxLds) return;
     const size_t vec = es * (size_t)ga.R * (size_t)ga.N;
     const int64_t room = (int64_t)((ga.lay.off_cval - ga.lay.off_ckpt) / vec);
     const int32_t nb = (ga.L + (1 << ga.cls.lb) - 1) >> ga.cls.lb;

@@ -62,6 +62,9 @@ __host__ __device__ constexpr int grad_class_waves_per_simd(int nslot, int ks, i
     return w > 8 ? 8 : (w < 1 ? 1 : w);
 }
 constexpr int kGradClassMaxWaves = 4;
+// Most local memory a group may take; where a kernel needs its limit raised, it
+// is raised to this, one value whatever the launch (see launch_csweep_one).
+constexpr size_t kGradClassMaxLds = 128 * 1024;
 // LDS bytes: class sums of every wave while donors are added up, then (P, Q)
 // every eight variants, then (P', Q').
 inline size_t grad_class_lds(int ks, int lb, int nwaves, size_t tsize) {
@@ -468,12 +471,14 @@ hipError_t launch_grad_class_one(const GradArgs &ga, const GradClassArgs &a, int
     if (nwaves < 1 || nwaves > kGradClassMaxWaves || (int64_t)nwaves * NSLOT * 64 < a.N)
         return hipErrorInvalidValue;
     const size_t lds = grad_class_lds(KS, a.lb, nwaves, sizeof(T));
+    if (lds > kGradClassMaxLds) return hipErrorInvalidValue;
     char *ws = ga.ws;
     const GradLayout &Ly = ga.lay;
     auto go = [&](auto kern) {
         if (lds > 65536) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)kGradClassMaxLds);
             if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL(kern, dim3(a.R), dim3(64 * nwaves), lds, st, c.ids, c.keys, c.cnt, c.rows,

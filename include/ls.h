@@ -107,7 +107,7 @@ typedef struct {
     const uint64_t *Hr;   /* device: internal row layout in the workspace */
     int64_t hr_stride;    /* 64-bit words per internal row */
     int32_t nf;           /* number of full 64-haplotype words: floor(N/64) */
-    int32_t reserved;     /* haplotype classes: 0, or block length and words */
+    int32_t reserved;     /* haplotype classes: 0, or block length, precisions and words */
     /* optional, set by the caller before ls_model_init: */
     const double *mu_vec; /* device, [L] mutation probability per variant (the
                              paper's vector mu, section 3.4), each in [0, 1],
@@ -140,9 +140,9 @@ typedef struct {
  * rows (about 2 N L / 8 bytes), the per-variant FP32 transition
  * coefficients of the sweeps (40 L bytes), the per-variant emission
  * tables for a vector mu (32 L + 8 bytes), the checks of a prior matrix
- * (16 N bytes) and, for N >= 512 and L >= 64, the haplotype classes of
- * blocks of variants (about N L / 8 bytes for the donors' classes and up to
- * L min(N/4, 2048) bytes for the classes themselves) into. A workspace that
+ * (16 N bytes) and, for 512 <= N <= 81,920 and L >= 64, the haplotype classes
+ * of blocks of variants (about N L / 8 bytes for the donors' classes and up to
+ * 0.9 L min(N/4, 1024) bytes for the classes themselves) into. A workspace that
  * lacks room for the classes alone is accepted; sweeps then run without
  * them. */
 size_t ls_model_workspace_bytes(int32_t N, int32_t L);
@@ -153,7 +153,8 @@ size_t ls_model_workspace_bytes(int32_t N, int32_t L);
  * stream). The workspace must stay allocated and unchanged while the model
  * is used. Where the haplotypes repeat within blocks of variants, long moves
  * of FP32 and FP64 tables (64 variants or more, uniform prior, rho <= 0.9,
- * 2^-30 <= mu <= 1/2) are carried per class of equal haplotypes; their
+ * 2^-30 <= mu <= 1/2, and no run of near-zero rho long enough for a donor's
+ * share to leave the precision's range) are carried per class of equal haplotypes; their
  * results agree with the other sweeps' to rounding, and a long move cut into
  * several agrees with the whole one to rounding. Errors: LS_ERR_ARG (NULL H/rho, N < 2, L < 1, mu or rho out of
  * range, short stride), LS_ERR_WORKSPACE, LS_ERR_DEVICE. */

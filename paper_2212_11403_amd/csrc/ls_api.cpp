@@ -586,24 +586,35 @@ ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *str
     if (!workspace || ws_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255))
         return LS_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
-    std::vector<double> rho((size_t)std::max(m->L - 1, 0));
-    if (!rho.empty()) {
-        hipError_t e = hipMemcpyAsync(rho.data(), m->rho, rho.size() * sizeof(double),
-                                      hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) return LS_ERR_DEVICE;
-        for (double r : rho)
-            if (!(r >= 0.0 && r <= 1.0)) return LS_ERR_ARG;
-    }
-    std::vector<double> muv(m->mu_vec ? (size_t)m->L : 0);
-    if (!muv.empty()) {
-        hipError_t e = hipMemcpyAsync(muv.data(), m->mu_vec, muv.size() * sizeof(double),
-                                      hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) return LS_ERR_DEVICE;
-        for (double x : muv)
-            if (!(x >= 0.0 && x <= 1.0)) return LS_ERR_ARG;
-    }
+    // The rows are laid out and their classes counted first, so that the counts
+    // come to the host with the parameters, at one wait. Both depend on H alone
+    // and leave a model of the same H on this workspace as it is.
+    const int64_t hs = hr_stride_for(m->N);
+    uint64_t *Hr = static_cast<uint64_t *>(workspace);
+    auto mu_fits = [](double mu) { return mu <= 0.5 && mu >= 0x1p-30; };
+    bool in_range = lsk::class_section(m->N, m->L) && !m->prior &&
+                    ws_bytes >= ls_model_workspace_bytes(m->N, m->L) &&
+                    (m->mu_vec || mu_fits(m->mu));
+    char *const section = static_cast<char *>(workspace) + class_offset_bytes(m->N, m->L);
+    const lsk::ClassLayout lay = in_range ? lsk::class_layout(m->N, m->L) : lsk::ClassLayout{};
+    int32_t *const most = in_range ? reinterpret_cast<int32_t *>(section + lay.off_max) : nullptr;
+    hipError_t e = lsk::launch_repack(m->H, m->stride_words, m->N, m->L, Hr, hs, most, st);
+    if (e == hipSuccess && in_range)
+        e = lsk::launch_class_count(Hr, hs, m->N, m->L, lsk::class_cap(m->N), most, st);
+    int32_t host_most[4] = {0, 0, 0, 0};
+    std::vector<double> rho((size_t)std::max(m->L - 1, 0)), muv(m->mu_vec ? (size_t)m->L : 0);
+    auto fetch = [&](void *to, const void *from, size_t n) {
+        if (e == hipSuccess && n > 0) e = hipMemcpyAsync(to, from, n, hipMemcpyDeviceToHost, st);
+    };
+    fetch(rho.data(), m->rho, rho.size() * sizeof(double));
+    fetch(muv.data(), m->mu_vec, muv.size() * sizeof(double));
+    fetch(host_most, most, in_range ? sizeof host_most : 0);
+    if (e == hipSuccess && (!rho.empty() || !muv.empty())) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return LS_ERR_DEVICE;
+    for (double r : rho)
+        if (!(r >= 0.0 && r <= 1.0)) return LS_ERR_ARG;
+    for (double x : muv)
+        if (!(x >= 0.0 && x <= 1.0)) return LS_ERR_ARG;
     uint64_t h = 1469598103934665603ull;
     h = fnv1a(h, &m->N, sizeof m->N);
     h = fnv1a(h, &m->L, sizeof m->L);
@@ -615,22 +626,30 @@ ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *str
         // per-column sums and hashes of the full contents go into the hash
         double *stats = reinterpret_cast<double *>(static_cast<char *>(workspace) +
                                                    prior_stats_offset_bytes(m->N, m->L));
-        std::vector<double> hs((size_t)m->N * 2);
-        hipError_t e = lsk::launch_prior_stats(m->prior, m->N, stats, st);
+        std::vector<double> sums((size_t)m->N * 2);
+        e = lsk::launch_prior_stats(m->prior, m->N, stats, st);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(hs.data(), stats, hs.size() * sizeof(double), hipMemcpyDeviceToHost,
-                               st);
+            e = hipMemcpyAsync(sums.data(), stats, sums.size() * sizeof(double),
+                               hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return LS_ERR_DEVICE;
         for (int32_t c = 0; c < m->N; ++c)
-            if (!(std::fabs(hs[2 * (size_t)c] - 1.0) <= 1e-9)) return LS_ERR_ARG;
-        h = fnv1a(h, hs.data(), hs.size() * sizeof(double));
+            if (!(std::fabs(sums[2 * (size_t)c] - 1.0) <= 1e-9)) return LS_ERR_ARG;
+        h = fnv1a(h, sums.data(), sums.size() * sizeof(double));
     }
     if (h == 0) h = 1;
-    const int64_t hs = hr_stride_for(m->N);
-    uint64_t *Hr = static_cast<uint64_t *>(workspace);
-    hipError_t e = lsk::launch_repack(m->H, m->stride_words, m->N, m->L, Hr, hs, st);
-    if (e != hipSuccess) return LS_ERR_DEVICE;
+    // haplotype classes: the class sweep keeps its sums in range with powers
+    // of two taken out once a step, which covers these parameters (a jump
+    // factor of at most 10 and an emission ratio of at least 2^-30), and the
+    // classes' values as far as share_fall's limits
+    for (size_t k = 0; in_range && k < muv.size(); ++k) in_range = mu_fits(muv[k]);
+    for (size_t k = 0; in_range && k < rho.size(); ++k) in_range = rho[k] <= 0.9;
+    int32_t plain = 0;
+    if (in_range) {
+        const double fall = share_fall(m->N, m->L, rho, m->mu, muv);
+        plain = (fall > kFallF32 ? kPlainF32 : 0) | (fall > kFallF64 ? kPlainF64 : 0);
+        in_range = plain != (kPlainF32 | kPlainF64);
+    }
     // forward tables: kappa and kappa / (N-1), times the emission divisor
     // (fill_scalars' forward cnum and bmul, with the divisor applied last,
     // so that a constant per-variant mu gives the scalar model's table)
@@ -657,37 +676,8 @@ ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *str
             reinterpret_cast<double *>(eb + 2 * L * (sizeof(double) + sizeof(float))), st);
         if (e != hipSuccess) return LS_ERR_DEVICE;
     }
-    // haplotype classes: the class sweep keeps its sums in range with powers
-    // of two taken out once a step, which covers these parameters (a jump
-    // factor of at most 10 and an emission ratio of at least 2^-30), and the
-    // classes' values as far as share_fall's limits
     int32_t classes = 0;
-    bool in_range = lsk::class_section(m->N, m->L) && ws_bytes >= ls_model_workspace_bytes(m->N, m->L) &&
-                    !m->prior;
-    auto mu_fits = [](double mu) { return mu <= 0.5 && mu >= 0x1p-30; };
-    if (in_range && !m->mu_vec) in_range = mu_fits(m->mu);
-    for (size_t k = 0; in_range && k < muv.size(); ++k) in_range = mu_fits(muv[k]);
-    for (size_t k = 0; in_range && k < rho.size(); ++k) in_range = rho[k] <= 0.9;
-    int32_t plain = 0;
     if (in_range) {
-        const double fall = share_fall(m->N, m->L, rho, m->mu, muv);
-        plain = (fall > kFallF32 ? kPlainF32 : 0) | (fall > kFallF64 ? kPlainF64 : 0);
-        in_range = plain != (kPlainF32 | kPlainF64);
-    }
-    // (and past N = 81,920 no class sweep holds the donors in registers)
-    int ns = 0, nw = 0;
-    if (in_range && class_shape(m->N, LS_FP32, 2, &ns, &nw)) {
-        char *section = static_cast<char *>(workspace) + class_offset_bytes(m->N, m->L);
-        const lsk::ClassLayout lay = lsk::class_layout(m->N, m->L);
-        int32_t *most = reinterpret_cast<int32_t *>(section + lay.off_max);
-        e = lsk::launch_fill_u32(reinterpret_cast<uint32_t *>(most), 0u, 4, st);
-        for (int b = 0; b < 3 && e == hipSuccess; ++b)
-            e = lsk::launch_class_count(Hr, hs, m->N, m->L, 4 + b, lsk::class_cap(m->N), most + b, st);
-        int32_t host_most[4];
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(host_most, most, sizeof host_most, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) return LS_ERR_DEVICE;
         classes = choose_classes(m->N, host_most);
         if (classes) {
             e = lsk::launch_class_build(Hr, hs, m->N, m->L, classes & 255, classes >> 8, section, lay, st);

@@ -41,6 +41,7 @@ __host__ __device__ constexpr int csweep_max_waves(int nslot, int ks, int vgpr_p
 
 constexpr int kClassMinB = 16;   // shortest block
 constexpr int kClassMinN = 512;  // below, one wave holds few donors: no gain
+constexpr int kClassMaxN = 64 * 8 * 160;  // above, no class sweep holds the donors in registers
 constexpr int kClassMinL = 64;
 
 // Most classes a block may have: at most a quarter of the donors (more
@@ -49,7 +50,9 @@ inline int32_t class_cap(int32_t N) {
     const int32_t k = N / 4 / 64 * 64;
     return k < 64 * kClassMaxWords ? k : 64 * kClassMaxWords;
 }
-inline bool class_section(int32_t N, int32_t L) { return N >= kClassMinN && L >= kClassMinL; }
+inline bool class_section(int32_t N, int32_t L) {
+    return N >= kClassMinN && N <= kClassMaxN && L >= kClassMinL;
+}
 
 // Byte offsets of the class section of the model workspace, from its start
 // (256-byte aligned). Arrays over blocks are sized for the shortest block.
@@ -88,9 +91,10 @@ inline ClassLayout class_layout(int32_t N, int32_t L) {
     return c;
 }
 
-// Largest class count of any block for block length 2^lb into *most (atomic
-// maximum; above `cap`: more than cap). `most` holds 0 before.
-hipError_t launch_class_count(const uint64_t *Hr, int64_t hr_stride, int32_t N, int32_t L, int lb,
+// Largest class count of any block of 16, 32 and 64 variants into most[0..2]
+// (atomic maxima; above `cap`: more than cap, for this length or a shorter
+// one). `most` holds 0 before.
+hipError_t launch_class_count(const uint64_t *Hr, int64_t hr_stride, int32_t N, int32_t L,
                               int32_t cap, int32_t *most, hipStream_t st);
 // Classes of every block of length 2^lb, at most 64 kw each (kw words a row).
 hipError_t launch_class_build(const uint64_t *Hr, int64_t hr_stride, int32_t N, int32_t L, int lb,

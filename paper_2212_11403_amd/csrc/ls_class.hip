@@ -76,18 +76,33 @@ __device__ __forceinline__ int find_slot(uint64_t key, unsigned long long *tab, 
 
 }  // namespace
 
-// One workgroup per block of variants.
+// One workgroup per block of variants, blocks of 16 first, then those of 32 and
+// 64, in one launch (three launches left most of the card idle on short
+// models). A block has at least the classes of its parts, so once a block has
+// too many, blocks of that length and longer ones are not counted any more.
 __global__ void __launch_bounds__(1024)
-class_count_kernel(const uint64_t *__restrict__ Hr, int64_t stride, int32_t N, int32_t L, int lb,
-                   int HS, int cap, int32_t *most) {
+class_count_kernel(const uint64_t *__restrict__ Hr, int64_t stride, int32_t N, int32_t L, int HS,
+                   int cap, int32_t *most) {
     extern __shared__ unsigned long long tab[];
-    __shared__ int count, extra;
-    const int l0 = blockIdx.x << lb;
-    const int n = min(1 << lb, L - l0);
+    __shared__ int count, extra, skip;
+    int blk = blockIdx.x, len = 0;  // length 16 << len
+    for (; len < 2; ++len) {
+        const int blocks = (L + (16 << len) - 1) >> (4 + len);
+        if (blk < blocks) break;
+        blk -= blocks;
+    }
+    const int l0 = blk << (4 + len);
+    const int n = min(16 << len, L - l0);
     const int NF = N >> 6;
     for (int k = threadIdx.x; k < HS; k += 1024) tab[k] = kEmpty;
-    if (threadIdx.x == 0) count = extra = 0;
+    if (threadIdx.x == 0) {  // one thread asks, so that all of them agree
+        count = extra = skip = 0;
+        for (int k = 0; k <= len; ++k)
+            if (__hip_atomic_load(&most[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > cap) skip = 1;
+        if (skip) atomicMax(&most[len], cap + 1);
+    }
     __syncthreads();
+    if (skip) return;
     const int lane = threadIdx.x & 63;
     for (int word = uniform(threadIdx.x >> 6); word * 64 < N; word += 16) {
         if (*(volatile int *)&count > cap) break;
@@ -95,7 +110,7 @@ class_count_kernel(const uint64_t *__restrict__ Hr, int64_t stride, int32_t N, i
         if (word * 64 + lane < N) find_slot(key, tab, HS, cap, &count, &extra);
     }
     __syncthreads();
-    if (threadIdx.x == 0) atomicMax(most, count);
+    if (threadIdx.x == 0) atomicMax(&most[len], count);
 }
 
 // Numbers the classes of a block by their first member (so the numbering
@@ -184,12 +199,13 @@ class_build_kernel(const uint64_t *__restrict__ Hr, int64_t stride, int32_t N, i
     }
 }
 
-hipError_t launch_class_count(const uint64_t *Hr, int64_t hr_stride, int32_t N, int32_t L, int lb,
+hipError_t launch_class_count(const uint64_t *Hr, int64_t hr_stride, int32_t N, int32_t L,
                               int32_t cap, int32_t *most, hipStream_t st) {
     const int HS = hash_slots(cap);
-    const int blocks = (L + (1 << lb) - 1) >> lb;
+    int blocks = 0;
+    for (int lb = 4; lb <= 6; ++lb) blocks += (L + (1 << lb) - 1) >> lb;
     hipLaunchKernelGGL(class_count_kernel, dim3(blocks), dim3(1024), HS * sizeof(uint64_t), st, Hr,
-                       hr_stride, N, L, lb, HS, cap, most);
+                       hr_stride, N, L, HS, cap, most);
     return hipGetLastError();
 }
 

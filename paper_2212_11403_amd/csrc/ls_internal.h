@@ -245,7 +245,7 @@ struct CoefScalars {
 hipError_t launch_coef_tables(const double *rho, const double *mu_vec, int32_t L,
                               const CoefScalars &cs, float *out, hipStream_t st);
 hipError_t launch_repack(const uint32_t *H, int64_t stride_words, int32_t N, int32_t L,
-                         uint64_t *Hr, int64_t hr_stride, hipStream_t st);
+                         uint64_t *Hr, int64_t hr_stride, int32_t *zero, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st);
 // Emission tables of a per-variant mu (ls_misc.hip), after the coefficient
 // tables: [L][2] FP64 (match, mismatch) for the FP64 sweep, [L][2] FP32 pairs

@@ -10,9 +10,12 @@ namespace lsk {
 // Internal rows: row l holds the full 64-haplotype words W_0..W_{NF-1} twice
 // in a row, then the partial last word (bits past N cleared), then zeros:
 //   Hr[l][q] = W_{q mod NF}  (q < 2 NF),  Hr[l][2 NF] = partial word.
-// The sweep reads a recipient's rotated words as one contiguous run.
+// The sweep reads a recipient's rotated words as one contiguous run. `zero` (may
+// be null): four words set to 0, the class counts that come next.
 __global__ void repack_kernel(const uint32_t *__restrict__ H, int64_t stride_words, int32_t N,
-                              int32_t L, uint64_t *__restrict__ Hr, int64_t hr_stride) {
+                              int32_t L, uint64_t *__restrict__ Hr, int64_t hr_stride,
+                              int32_t *zero) {
+    if (zero && blockIdx.x == 0 && threadIdx.x < 4) zero[threadIdx.x] = 0;
     const int64_t total = (int64_t)L * hr_stride;
     const int NF = N >> 6;
     for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
@@ -35,13 +38,13 @@ __global__ void repack_kernel(const uint32_t *__restrict__ H, int64_t stride_wor
 }
 
 hipError_t launch_repack(const uint32_t *H, int64_t stride_words, int32_t N, int32_t L,
-                         uint64_t *Hr, int64_t hr_stride, hipStream_t st) {
+                         uint64_t *Hr, int64_t hr_stride, int32_t *zero, hipStream_t st) {
     const int64_t total = (int64_t)L * hr_stride;
     int64_t blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(repack_kernel, dim3((unsigned)blocks), dim3(256), 0, st, H, stride_words,
-                       N, L, Hr, hr_stride);
+                       N, L, Hr, hr_stride, zero);
     return hipGetLastError();
 }
 

@@ -484,7 +484,8 @@ hipError_t launch_sweep(int prec, int dir, const SweepPtrs &p, const SweepArgs &
 
 // Variants per sweep launch. A long sweep is split into launches of at most
 // this many variants, each resuming from the table the previous one left
-// (resumption is exact in every precision). Every launch starts all groups at
+// (exactly, in every precision of the plain sweeps; to rounding in the class
+// sweeps, so their results depend on this length). Every launch starts all groups at
 // the same variant; within one long launch the groups drift apart, the rows
 // they read at any moment spread beyond the L2 cache and the scalar row loads
 // fall through to the last-level cache. Measured backward sweep at N = 10,000,
@@ -495,13 +496,17 @@ hipError_t launch_sweep(int prec, int dir, const SweepPtrs &p, const SweepArgs &
 // with, and they are split the same way.
 constexpr int32_t kSweepChunk = 2048;
 
-// The chunk length (LS_SWEEP_CHUNK overrides it, for tuning).
-int32_t sweep_chunk() {
+// The chunk length (LS_SWEEP_CHUNK overrides it, for tuning). Class sweeps over
+// blocks of 2^lb variants (lb > 0) keep to what the checkpoints of a launch
+// allow with one at every block end, so that a gradient's launches end where
+// the log-likelihood's do, whatever its checkpoints.
+int32_t sweep_chunk(int lb) {
+    int32_t chunk = kSweepChunk;
     if (const char *env = std::getenv("LS_SWEEP_CHUNK")) {
         const int v = std::atoi(env);
-        if (v >= 1) return v;
+        if (v >= 1) chunk = v;
     }
-    return kSweepChunk;
+    return lb > 0 ? std::min(chunk, (lsk::kMaxTargets - 1) << lb) : chunk;
 }
 
 hipError_t run_chunks(int prec, int dir, const SweepPtrs &p, const SweepArgs &a, Shape sh,
@@ -509,7 +514,7 @@ hipError_t run_chunks(int prec, int dir, const SweepPtrs &p, const SweepArgs &a,
     SweepArgs c = a;
     int32_t l0 = a.l0;
     int next = 0;  // next target, in travel order
-    const int32_t chunk = sweep_chunk();
+    const int32_t chunk = sweep_chunk(cls ? cls->lb : 0);
     for (;;) {
         int32_t tc;
         if (dir == 0) {
@@ -1049,7 +1054,7 @@ ls_status loglik_grad_impl(const ls_model *m, const int32_t *recipients, int32_t
         class_ptrs(m, prec, ga.cls);
         ga.class_lu_prefix = log_unit_prefix(m);
     }
-    ga.chunk = sweep_chunk();
+    ga.chunk = sweep_chunk(ga.by_class ? ga.cls.lb : 0);
     if (!choose_shape(m->N, prec, &ga.fwd_shape, false, m->prior != nullptr))
         return LS_ERR_UNSUPPORTED;
     ga.prior = m->prior;

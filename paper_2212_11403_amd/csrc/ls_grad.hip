@@ -232,8 +232,10 @@ hipError_t launch_grad(const GradArgs &ga, int prec, Shape sh, double *loglik, d
         // makes (at most ga.chunk variants each, resuming from the table), so
         // log P is bit-identical to that of the log-likelihood alone. A launch
         // holds at most chunk / seg + 1 <= sqrt(chunk) + 1 checkpoints (with an
-        // oversized chunk, a launch ends at its 256th checkpoint).
-        // The class adjoint takes the ends of (groups of) blocks instead.
+        // oversized chunk, a launch ends at its 256th checkpoint, which leaves
+        // the plain sweep's bits as they are). The class adjoint takes the ends
+        // of (groups of) blocks instead; the chunk of class sweeps is short
+        // enough for all of a launch's (sweep_chunk in ls_api.cpp).
         std::vector<int32_t> tl(2 * kMaxTargets);
         int l0 = -1, knext = 0;
         const int kept = ga.cg_nslot ? (ga.cg_blocks - 1) / ga.cg_group : ga.nseg;

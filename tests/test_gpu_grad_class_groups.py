@@ -106,3 +106,19 @@ def test_workspace_without_classes(ls):  # noqa: F811
         assert torch.equal(a["P"], b["P"]) and torch.equal(a["fwd"].log_scale, b["fwd"].log_scale)
         g, k = (ls.loglik_grad(x, None, prec) for x in (m, small))
         assert torch.equal(g["grad_rho"], k["grad_rho"]) and torch.equal(g["grad_mu"], k["grad_mu"])
+
+
+def test_long_launches(ls, monkeypatch):  # noqa: F811
+    """Launches meant to be longer than one launch's checkpoints: log P of the
+    gradient is still that of the log-likelihood alone, bit for bit."""
+    import torch
+    N, L = 520, 60_000
+    H, rho, mu = _case(N, L, 4, seed=1)
+    m = ls.Model(H, N, rho, mu)
+    ends, room = _groups(m)
+    assert ends > 2 * 256 and room > 256  # more than 256 checkpoints kept
+    rec = np.array([0, 300, N - 1], np.int32)
+    monkeypatch.setenv("LS_SWEEP_CHUNK", "1000000")
+    for prec in ("fp64", "fp32"):
+        g, p = (ls.loglik_grad(m, rec, prec, grad=grad) for grad in (True, False))
+        assert torch.equal(g["loglik"], p["loglik"])

@@ -152,12 +152,13 @@ size_t ls_model_workspace_bytes(int32_t N, int32_t L);
  * aligned) on `stream`. Reads rho back to the host (synchronises the
  * stream). The workspace must stay allocated and unchanged while the model
  * is used. Where the haplotypes repeat within blocks of variants, long moves
- * of FP32 and FP64 tables (64 variants or more, uniform prior, rho <= 0.9,
- * 2^-30 <= mu <= 1/2, and no run of near-zero rho long enough for a donor's
- * share to leave the precision's range) are carried per class of equal haplotypes; their
- * results agree with the other sweeps' to rounding, and a long move cut into
- * several agrees with the whole one to rounding. Errors: LS_ERR_ARG (NULL H/rho, N < 2, L < 1, mu or rho out of
- * range, short stride), LS_ERR_WORKSPACE, LS_ERR_DEVICE. */
+ * of FP32 and FP64 tables (64 variants or more, at most one target per eight
+ * of them, uniform prior, rho <= 0.9, 2^-30 <= mu <= 1/2, and no run of
+ * near-zero rho long enough for a donor's share to leave the precision's
+ * range) are carried per class of equal haplotypes; their results agree with
+ * the other sweeps' to rounding, and a long move cut into several agrees with
+ * the whole one to rounding. Errors: LS_ERR_ARG (NULL H/rho, N < 2, L < 1, mu
+ * or rho out of range, short stride), LS_ERR_WORKSPACE, LS_ERR_DEVICE. */
 ls_status ls_model_init(ls_model *m, void *workspace, size_t ws_bytes, void *stream);
 
 /* A forward or backward table for R recipients at one variant (cf. the

@@ -320,9 +320,17 @@ int32_t choose_classes(int32_t N, const int32_t most[3]) {
 // resume to the same bits wherever a move is cut (the class sweep's agree to
 // rounding); a block boundary also costs as much as several plain steps.
 constexpr int kClassMinMove = 64;
+// Every target writes the whole donor vector, which the plain sweep has at hand
+// and the class sweep forms donor by donor, as at a block boundary. With more
+// than one target per eight variants the plain sweep is the faster (backward
+// moves over 260 variants, FP32, us, class / plain: N = 10,000, 64 recipients, 32
+// targets 287 / 290, 64 386 / 337, 256 1,187 / 615; N = 20,000 298 / 302, 441 /
+// 359, 1,289 / 660).
+constexpr int kClassTargetGap = 8;
 
-bool class_route(const ls_model *m, int prec, int variants) {
+bool class_route(const ls_model *m, int prec, int variants, int targets = 0) {
     if (class_lb(m) == 0 || m->prior || variants < kClassMinMove) return false;
+    if (variants < kClassTargetGap * targets) return false;
     if (prec != LS_FP32 && prec != LS_FP64) return false;
     if (m->reserved & (prec == LS_FP64 ? kPlainF64 : kPlainF32)) return false;
     // (the block length is chosen for FP32)
@@ -807,7 +815,7 @@ ls_status forward_impl(ls_table *fwd, const ls_model *m, int32_t t, const int32_
     p.snap = want_out ? stage : fwd->state;
     hipStream_t st = as_stream(stream);
     lsk::ClassPtrs cls;
-    const bool by_class = class_route(m, fwd->prec, t - std::max(fwd->l, 0));
+    const bool by_class = class_route(m, fwd->prec, t - std::max(fwd->l, 0), a.nt);
     if (by_class) class_ptrs(m, fwd->prec, cls), p.lu_prefix = log_unit_prefix(m);
     hipError_t e = launch_sweep_chunked(fwd->prec, 0, p, a, sh, st, by_class ? &cls : nullptr);
     if (e != hipSuccess) return LS_ERR_DEVICE;
@@ -874,7 +882,7 @@ ls_status ls_backward(ls_table *bck, const ls_model *m, int32_t t, const int32_t
     p.status = bck->status;
     p.snap = T > 0 ? bsnap : bck->state;
     lsk::ClassPtrs cls;
-    const bool by_class = class_route(m, bck->prec, top - t);
+    const bool by_class = class_route(m, bck->prec, top - t, T);
     if (by_class) class_ptrs(m, bck->prec, cls), p.lu_prefix = log_unit_prefix(m);
     hipError_t e = launch_sweep_chunked(bck->prec, 1, p, a, sh, as_stream(stream),
                                         by_class ? &cls : nullptr);

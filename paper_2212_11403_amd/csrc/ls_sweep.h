@@ -452,38 +452,79 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         }
         quantise();
     };
-    // v <- theta^l (.) v; returns this lane's partial sums
-    auto emit = [&](int l) __attribute__((always_inline)) -> Part {
+    // v <- theta^l (.) v; returns this lane's partial sums. The scalars of the
+    // variant are read here unless the caller has them (`ahead`).
+    auto emit = [&](int l, uint64_t sw_bits, T em, T ex, const Words &wx, auto ahead)
+                    __attribute__((always_inline)) -> Part {
+        constexpr bool HAVE = decltype(ahead)::value;
         const uint64_t *row = Hr + (int64_t)l * a.hr_stride;
-        T em, ex, ta, tb;
-        emis_at(l, em, ex);
+        T ta, tb;
+        if constexpr (!HAVE) emis_at(l, em, ex);
         Acc acc;
         acc_start(acc);
         if constexpr (XMUL) {
             T r;
             uint64_t flip;
-            xmul_params(row[self_off], em, ex, r, flip);
-            xmul_all([&](int s) __attribute__((always_inline)) { return mask_of(row, s); }, flip, r);
+            xmul_params(HAVE ? sw_bits : row[self_off], em, ex, r, flip);
+            xmul_all([&](int s) __attribute__((always_inline)) {
+                if constexpr (HAVE) return step_mask(row, wx, s);
+                else return mask_of(row, s);
+            }, flip, r);
 #pragma unroll
             for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc);
             if constexpr (SNORM) part_w = aw0 + aw1;
             return acc_parts(acc);
         }
-        thetas(row[self_off], em, ex, ta, tb);
+        thetas(HAVE ? sw_bits : row[self_off], em, ex, ta, tb);
 #pragma unroll
         for (int s = 0; s < NSLOT; ++s) {
-            const T th = lane_bit(mask_of(row, s)) ? tb : ta;
+            uint64_t word;
+            if constexpr (HAVE) word = step_mask(row, wx, s);
+            else word = mask_of(row, s);
+            const T th = lane_bit(word) ? tb : ta;
             const T nv = th * v[s];
             v[s] = nv;
             account_sum(s, nv, acc);
         }
         return acc_parts(acc);
     };
+    // Narrow single-wave groups keep the element of a row that each lane and slot
+    // writes at a target (one past every row for lanes without a donor, whose
+    // store the buffer's range check drops); the others form it at each store.
+    // With it and what is read ahead kept over a target (below), backward moves
+    // of 8 recipients over 260 variants with 256 targets take, in us, FP32 N = 200
+    // 225 -> 133 (163 in several waves), N = 500 308 -> 180 (194). FP64 waves of 24
+    // and 28 slots took 10 to 20% longer without targets when they kept it.
+    constexpr bool KEEP_AT = ONE && NSLOT <= (sizeof(T) == 8 && !PI ? 20 : 8) && !EVERY;
+    int row_at[KEEP_AT ? NSLOT : 1];
+    if constexpr (KEEP_AT) {
+#pragma unroll
+        for (int s = 0; s < NSLOT; ++s) {
+            if (s < NR) {
+                int w = reg_base + s;
+                if (w >= NF) w -= NF;
+                row_at[s] = w * 64 + lane;
+            } else {
+                SpecSlot sp = special_slot(s, NF, N, g, self_full, sw, self_bit);
+                row_at[s] = lane_bit(sp.valid) ? sp.word * 64 + lane : 0x0ffffff0;
+            }
+        }
+    }
     // write v (times `scale`, as type D) to a row of N elements starting at
     // `dst`; the diagonal entry is written as 0 and lanes past N are skipped
     auto store_row = [&](auto *dst, T scale) __attribute__((always_inline)) {
         using D = typename std::remove_pointer<decltype(dst)>::type;
         const rsrc_t rs = make_rsrc(dst, (uint32_t)N * sizeof(D));
+        if constexpr (KEEP_AT) {
+#pragma unroll
+            for (int s = 0; s < NSLOT; ++s) {
+                T x = (T)v[s] * scale;
+                if (s == 0 && NR > 0) x = lane_bit(m0) ? x : (T)0;
+                if (s >= NR) x = spec_keep[s - NR] != (T)0 ? x : (T)0;
+                buf_store((D)x, rs, row_at[s] * (int)sizeof(D), 0, kStreaming);
+            }
+            return;
+        }
         const int voff = lane * (int)sizeof(D);
         const int rb = opaque(reg_base);
 #pragma unroll
@@ -744,6 +785,35 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 // past it, they would hold a second copy of the column live
                 __builtin_amdgcn_sched_barrier(0);
             }
+        } else if constexpr (AHEAD) {
+            // the same as below with what is read ahead kept over a target: the
+            // steps are short, and a target would cost a wait of its own
+            T em_nx, ex_nx;
+            Coef q_nx;
+            uint64_t w_nx;
+            Words x_nx;
+            auto read_ahead = [&](int ln) __attribute__((always_inline)) {
+                coef_read(ln, q_nx);
+                emis_at(ln, em_nx, ex_nx);
+                w_nx = self_word(ln);
+                x_nx = words_at(ln);
+            };
+            read_ahead(l <= lmax ? l : lmax);
+            for (;;) {
+                const int lend = kt < a.nt ? a.tgt_l[kt] : a.t;
+                for (; l <= lend; ++l) {
+                    T A, b;
+                    coef_form(l, q_nx, A, b);
+                    const T em = em_nx, ex = ex_nx;
+                    const uint64_t wb = w_nx;
+                    const Words wx = x_nx;
+                    read_ahead(l < lmax ? l + 1 : lmax);
+                    S = reduce(step(l, wb, em, ex, coef_c(A, S), b, wx));
+                    account(S);
+                }
+                if (kt < a.nt) snapshot();
+                if (lend >= a.t) break;
+            }
         } else for (;;) {
             const int lend = kt < a.nt ? a.tgt_l[kt] : a.t;
             T em_nx, ex_nx;
@@ -782,10 +852,55 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         const int lstart = fresh ? a.L - 1 : a.l0;
         if (fresh) affine((T)0, (T)a.kappa);
         if (kt < a.nt && a.tgt_l[kt] == lstart) snapshot();
-        if (a.t < lstart) {
+        if constexpr (AHEAD) {
+            if (a.t < lstart) {
+                // as below, with what is read ahead kept over a target, as in the forward
+                T em_nx, ex_nx;
+                Coef q_nx;
+                uint64_t w_nx;
+                Words x_nx;
+                auto read_ahead = [&](int ln) __attribute__((always_inline)) {
+                    coef_read(ln, q_nx);
+                    emis_at(ln, em_nx, ex_nx);
+                    w_nx = self_word(ln);
+                    x_nx = words_at(ln);
+                };
+                S = reduce(emit(lstart, 0, (T)0, (T)0, Words{}, std::false_type{}));
+                account(S);
+                int l = lstart - 1;
+                read_ahead(l);
+                for (;; --l) {
+                    const int lend = kt < a.nt ? a.tgt_l[kt] : a.t;
+                    T A, B, em, ex, c, b;
+                    uint64_t wb;
+                    Words wx;
+                    auto take = [&]() __attribute__((always_inline)) {
+                        coef_form(l, q_nx, A, B);
+                        em = em_nx;
+                        ex = ex_nx;
+                        wb = w_nx;
+                        wx = x_nx;
+                        read_ahead(l > 0 ? l - 1 : 0);
+                        c = coef_c(A, S);
+                        b = SNORM ? coef_c(B * Wsum, S) : B;
+                    };
+                    for (; l > lend; --l) {
+                        take();
+                        S = reduce(step(l, wb, em, ex, c, b, wx));
+                        account(S);
+                    }
+                    take();
+                    affine(c, b);
+                    if (kt < a.nt && a.tgt_l[kt] == l) snapshot();
+                    if (l <= a.t) break;
+                    S = reduce(emit(l, wb, em, ex, wx, std::true_type{}));
+                    account(S);
+                }
+            }
+        } else if (a.t < lstart) {
             // each column sum enters the log scale right after its
             // reduction (off the path to the next step's coefficients)
-            Part part = emit(lstart);
+            Part part = emit(lstart, 0, (T)0, (T)0, Words{}, std::false_type{});
             S = reduce(part);
             account(S);
             int l = lstart - 1;
@@ -824,7 +939,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 affine(c, b);
                 if (kt < a.nt && a.tgt_l[kt] == l) snapshot();
                 if (l <= a.t) break;
-                part = emit(l);
+                part = emit(l, 0, (T)0, (T)0, Words{}, std::false_type{});
                 S = reduce(part);
                 account(S);
                 --l;

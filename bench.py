@@ -484,7 +484,7 @@ def main():
               "launch_ms": launch_s * 1e3}
     if model.c.reserved:
         # haplotype classes: blocks of `block` variants, `words` x 64 classes
-        block, words = 1 << (model.c.reserved & 255), model.c.reserved >> 8
+        block, words = 1 << (model.c.reserved & 7), model.c.reserved >> 8
         steps = cells_launch / N                       # recipients x variants
         lds = CLASS_LDS_BYTES_PER_DONOR * cells_launch / block / launch_s
         flops = (CLASS_FLOPS_PER_CLASS * 64 * words * steps +

@@ -87,7 +87,7 @@ struct Shape {
 };
 
 // Slots per wave of the several-wave form of a single wave of `nslot` slots in
-// FP32 arithmetic, 0 if it has none: three or four waves, whose sums one wave
+// FP32, 0 if it has none: three or four waves, whose sums one wave
 // forms side by side.
 __host__ __device__ constexpr int split_slots(int nslot) {
     return nslot < 12 || nslot > 32 || nslot % 4 != 0 ? 0 : (nslot <= 16 ? 4 : 8);

@@ -131,16 +131,13 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     // kappa, inside half's range, whatever the prior)
     constexpr bool SNORM = QH && PI && DIR == 1;
     static_assert(!QH || XMUL, "FP16-stored sweeps use the masked emission");
-    // single-wave groups in FP32 arithmetic that have a several-wave form (NP
-    // waves of SL slots, run_shape) add the column as it does: NP partial sums
-    // (of 20 and 28 slots: the last of its slots hold no donor and add 0)
-    constexpr bool kSplit = ONE && sizeof(T) == 4 && !EVERY && !PI && split_slots(NSLOT) > 0;
+    // FP32 single-wave groups that have a several-wave form (NP waves of SL
+    // slots, run_shape) add the column as it does: NP partial sums (of 20 and
+    // 28 slots: the last of its slots hold no donor and add 0). Not with
+    // FP16-stored vectors: their rounding after every update carries another
+    // order of the sum into the third digit.
+    constexpr bool kSplit = ONE && PT::id == 1 && !EVERY && !PI && split_slots(NSLOT) > 0;
     constexpr int SL = kSplit ? split_slots(NSLOT) : NSLOT, NP = kSplit ? split_waves(NSLOT) : 1;
-    // FP16-stored backward of either form: every slot's c v + b is rounded to
-    // half in one step (one instruction), so the lanes without a donor are
-    // masked after it; a multiply in between would round special slots twice
-    constexpr bool KEEP_LAST =
-        QH && DIR == 1 && !PI && (kSplit || (!ONE && (NSLOT == 4 || NSLOT == 8)));
     __shared__ T red[2 * kRedStride];
 
     const int nwaves = uniform(blockDim.x >> 6);
@@ -385,7 +382,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         flip = uniform((int)(rb != on_match)) ? ~0ull : 0ull;
     };
     auto xmul_all = [&](auto mask, uint64_t flip, T r) __attribute__((always_inline)) {
-        masked_scale_all<NSLOT, ONE>(v, mask, flip, r);
+        masked_scale_all<NSLOT, ONE && !QH>(v, mask, flip, r);
     };
     // v <- theta^l (.) (c v + b); returns this lane's partial sums
     auto step = [&](int l, uint64_t sw_bits, T em, T ex, T c, T b_s, const Words &wx)
@@ -402,8 +399,6 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             for (int s = 0; s < NSLOT; ++s) {
                 if constexpr (PI && DIR == 0) {
                     v[s] = fma(c, (T)v[s], b * pv[s]);
-                } else if constexpr (KEEP_LAST) {
-                    v[s] = fma(c, (T)v[s], b);
                 } else if constexpr (DIR == 1) {
                     v[s] = keep_lanes(s, fma(c, (T)v[s], b));
                 } else {
@@ -417,10 +412,6 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             // FP16 storage rounds what a table holds: the backward vector
             // kappa beta^l before its emission, the forward kappa alpha^l
             if constexpr (DIR == 1) quantise();
-            if constexpr (KEEP_LAST) {
-#pragma unroll
-                for (int s = 0; s < NSLOT; ++s) v[s] = keep_lanes(s, v[s]);
-            }
             xmul_all([&](int s) __attribute__((always_inline)) { return step_mask(row, wx, s); },
                      flip, r);
             if constexpr (DIR == 0) quantise();
@@ -446,10 +437,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     // v <- c v + b (no emission): the backward vector before theta^l
     auto affine = [&](T c, T b) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < NSLOT; ++s) {
-            if constexpr (KEEP_LAST) v[s] = keep_lanes(s, (T)(ST)fma(c, v[s], b));
-            else v[s] = keep_lanes(s, fma(c, v[s], b));
-        }
+        for (int s = 0; s < NSLOT; ++s) v[s] = keep_lanes(s, fma(c, v[s], b));
         quantise();
     };
     // v <- theta^l (.) v; returns this lane's partial sums. The scalars of the

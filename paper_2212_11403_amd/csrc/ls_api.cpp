@@ -143,32 +143,31 @@ double shape_cost(int32_t N, int prec, int ns, int nw, int wps = 0, bool sweep =
 // Panels of at most 2,048 haplotypes (the gradient's passes and sweeps with a
 // prior matrix: 512): one wave per recipient, with the fewest slots that hold
 // them. Their groups never fill the SIMDs, so a step costs its latency, which
-// the exchange between waves adds to (ls_sweep.h). In FP32 the waves of 12 slots
-// and more have a several-wave form with the same sums, which a launch over few
-// recipients runs (run_shape): there the work of one wave is the longer chain.
-// (FP16-stored vectors stay with one wave for few recipients too, at the price
-// in the table: another order of their sums shows in the third digit of a
-// posterior, so it may depend on N alone.) Measured in us per variant, forward / backward, all
-// recipients and (8 of them), against the group of several waves chosen by
-// shape_cost:
+// the exchange between waves adds to (ls_sweep.h). The shape depends on N and
+// the precision alone, so that recipients taken in windows give the bits of the
+// whole: it is the best for all recipients, and few of them pay for that above
+// 1,280 haplotypes in FP32 (backward) and 1,536 FP16-stored. Measured in us per
+// variant, forward / backward, all recipients and (8 of them), against the group
+// of several waves that shape_cost chooses:
 //   FP32  N = 300    0.29/0.25 (0.26/0.25)   against 0.49/0.42 (0.42/0.38)
-//             640    0.43/0.41 (0.39/0.36)           0.74/0.68 (0.44/0.43)
-//           1,000    0.46/0.47 (0.42/0.39)           0.61/0.57 (0.42/0.39)
-//           1,450    0.61/0.61 (0.50/0.43)           0.82/0.73 (0.50/0.43)
-//           2,000    0.65/0.65 (0.52/0.44)           0.79/0.74 (0.55/0.54)
-//   FP16      640    0.44/0.49 (0.40/0.44)           0.75/0.69 (0.46/0.44)
-//           1,000    0.50/0.49 (0.46/0.44)           0.63/0.59 (0.44/0.41)
-//           2,000    0.76/0.89 (0.78/0.76)           0.87/0.94 (0.63/0.60)
-//   FP64      500    0.33/0.29 (0.32/0.29)           0.51/0.48 (0.51/0.47)
-//           1,450    0.74/0.63 (0.57/0.50)           0.97/0.89 (0.61/0.59)
-//           2,000    0.84/0.75 (0.66/0.64)           0.88/0.83 (0.76/0.65)
+//             640    0.31/0.35 (0.30/0.34)           0.74/0.68 (0.44/0.43)
+//           1,000    0.35/0.40 (0.34/0.37)           0.61/0.57 (0.42/0.39)
+//           1,450    0.52/0.52 (0.46/0.50)           0.82/0.73 (0.50/0.43)
+//           2,000    0.62/0.58 (0.56/0.55)           0.79/0.74 (0.55/0.54)
+//   FP16      640    0.37/0.41 (0.35/0.37)           0.75/0.69 (0.46/0.44)
+//           1,000    0.41/0.37 (0.40/0.36)           0.63/0.59 (0.44/0.41)
+//           1,450    0.64/0.70 (0.52/0.54)           0.84/0.84 (0.55/0.51)
+//           2,000    0.77/0.81 (0.69/0.60)           0.88/0.94 (0.63/0.60)
+//   FP64      500    0.33/0.29 (0.32/0.29)           0.51/0.49 (0.51/0.47)
+//           1,000    0.42/0.43 (0.39/0.42)           0.57/0.51 (0.52/0.49)
+//           1,450    0.69/0.63 (0.50/0.50)           0.97/0.89 (0.62/0.59)
+//           2,000    0.81/0.73 (0.57/0.53)           0.88/0.83 (0.77/0.65)
 bool choose_one_wave(int32_t N, int prec, Shape *out, bool grad, bool prior) {
     const int words = (N + 63) / 64;
     if (words > (grad || prior ? 8 : lsk::kOneWaveSlots)) return false;
     for (int ns : menu(prec, grad))
         if (ns >= words && shape_fits(N, prec, ns, 1, prior)) {
-            const bool split = prec == LS_FP32 && !grad && !prior && lsk::split_slots(ns) > 0;
-            *out = Shape{ns, 1, split};
+            *out = Shape{ns, 1};
             return true;
         }
     return false;
@@ -184,7 +183,7 @@ bool choose_shape(int32_t N, int prec, Shape *out, bool grad = false, bool prior
     if (const char *env = std::getenv("LS_FORCE_SHAPE")) {
         int ns = 0, nw = 0;
         if (std::sscanf(env, "%d,%d", &ns, &nw) == 2 && shape_fits(N, prec, ns, nw, prior)) {
-            *out = Shape{ns, nw, false};
+            *out = Shape{ns, nw};
             return true;
         }
     }
@@ -210,7 +209,7 @@ bool choose_shape(int32_t N, int prec, Shape *out, bool grad = false, bool prior
         for (int nw = 1; nw <= lsk::kMaxWaves; ++nw)
             for (int ns : menu(prec, grad))
                 if (ok(ns, nw) && cost(ns, nw) <= best * 1.01) {
-                    *out = Shape{ns, nw, false};
+                    *out = Shape{ns, nw};
                     return true;
                 }
     }

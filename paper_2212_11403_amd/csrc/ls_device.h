@@ -83,11 +83,11 @@ __device__ __forceinline__ float wave_sum(float x) {
     return read_lane63(x);
 }
 
-// Four wave sums at once, each with the additions and order of wave_sum, left
-// in lane 63: the four chains are interleaved stage by stage, so each DPP read
-// comes three instructions after the write it depends on and needs no wait
-// states.
-__device__ __forceinline__ void wave_rows4(float &a, float &b, float &c, float &d) {
+// Four wave sums at once, each with the additions and order of wave_sum: the
+// four chains are interleaved stage by stage, so each DPP read comes three
+// instructions after the write it depends on and needs no wait states.
+__device__ __forceinline__ void wave_sum4(const float (&x)[4], float (&w)[4]) {
+    float a = x[0], b = x[1], c = x[2], d = x[3];
     a += dpp_f32<0xB1>(a);
     b += dpp_f32<0xB1>(b);
     c += dpp_f32<0xB1>(c);
@@ -116,22 +116,10 @@ __device__ __forceinline__ void wave_rows4(float &a, float &b, float &c, float &
         "v_add_f32_dpp %3, %3, %3 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
         "s_nop 1"
         : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
-}
-__device__ __forceinline__ void wave_sum4(const float (&x)[4], float (&w)[4]) {
-    float a = x[0], b = x[1], c = x[2], d = x[3];
-    wave_rows4(a, b, c, d);
     w[0] = read_lane63(a);
     w[1] = read_lane63(b);
     w[2] = read_lane63(c);
     w[3] = read_lane63(d);
-}
-// The sum block_sum forms over NP = 3 or 4 waves whose partials are x[0 .. NP-1]
-// of this wave: the same additions in the same order.
-template <int NP>
-__device__ __forceinline__ float waves_sum(const float (&x)[NP]) {
-    float a = x[0], b = x[1], c = x[2], d = NP > 3 ? x[NP - 1] : 0.0f;
-    wave_rows4(a, b, c, d);
-    return read_lane63((a + b) + (c + d));
 }
 __device__ __forceinline__ double wave_sum(double x) {
     x += dpp_f64<0xB1>(x);
@@ -436,15 +424,13 @@ __device__ __forceinline__ void sgpr_group16(const uint64_t (&m)[24]) {
 // v[s] <- r v[s] on the lanes of (mask(s) ^ flip), s < NS, in blocks of
 // 8, 4 and 1 slots; the last block carries the DPP wait states. From 64
 // slots up the 8-slot blocks go in groups of three whose row words are
-// loaded together (sgpr_group24). A single-wave group (ONE) of 16 or 32 slots
-// takes them in pairs: it has no other wave to cover a round trip per block
-// (FP64, N = 800 on 16 slots, 8 recipients: 15 to 20% less). Other slot counts
-// end with a short load all the same, and 24 and 28 slots took longer with
-// grouped ones.
-template <int NS, bool ONE, class T, class MaskFn>
+// loaded together (sgpr_group24). PAIRS (single-wave groups of 16 slots,
+// which have no other wave to cover a round trip per block): in groups of two
+// (FP64 backward, N = 800, 8 recipients: 0.44 -> 0.37 us per variant).
+template <int NS, bool PAIRS, class T, class MaskFn>
 __device__ __forceinline__ void masked_scale_all(T (&v)[NS], MaskFn mask, uint64_t flip, T r) {
     constexpr int N8 = NS / 8, N4 = (NS % 8) / 4, N1 = NS % 4;
-    constexpr int G = NS >= 64 ? 3 : (ONE && NS % 16 == 0 ? 2 : 1);  // 8-slot blocks per load group
+    constexpr int G = NS >= 64 ? 3 : (PAIRS && NS % 16 == 0 ? 2 : 1);  // 8-slot blocks per load group
 #pragma unroll
     for (int q0 = 0; q0 < N8; q0 += G) {
         const int ng = (N8 - q0) < G ? (N8 - q0) : G;

@@ -83,31 +83,28 @@ inline Emissions sweep_emissions(double mu) {
 struct Shape {
     int nslot;
     int nwaves;
-    bool split;  // one wave that may also run as several (run_shape)
 };
 
-// Slots per wave of the several-wave form of a single wave of `nslot` slots in
-// FP32, 0 if it has none: three or four waves, whose sums one wave
-// forms side by side.
-__host__ __device__ constexpr int split_slots(int nslot) {
-    return nslot < 12 || nslot > 32 || nslot % 4 != 0 ? 0 : (nslot <= 16 ? 4 : 8);
-}
-__host__ __device__ constexpr int split_waves(int nslot) {
-    return split_slots(nslot) == 0 ? 1 : (nslot + split_slots(nslot) - 1) / split_slots(nslot);
-}
-
-// The shape a sweep over `groups` recipients runs. The single wave has the
-// least work per step, the several waves the shorter step; the first wins
-// where the recipients fill the card, the second up to two groups per compute
-// unit. Both add the column in one order (kSplit in the sweep kernel), so
-// recipients taken in windows give the same bits either way. Measured in us
-// per variant, single wave / several, FP32: N = 640, 500 recipients 0.45 /
-// 0.42, 600 0.46 / 0.50; N = 2,048, 8 0.56 / 0.49, 500 0.61 / 0.53, 600 0.60 /
-// 0.61, all 0.69 / 1.11.
-constexpr int64_t kSplitGroups = 512;
-inline Shape run_shape(Shape sh, int64_t groups) {
-    if (!sh.split || groups > kSplitGroups) return sh;
-    return Shape{split_slots(sh.nslot), split_waves(sh.nslot), false};
+// Row words a single-wave sweep of `nslot` slots loads together at the top of a
+// step (ls_sweep.h), for the precision (ls_precision) and
+// direction (backward 1). From 20 slots up all of them at once spill scalar
+// registers; the counts are the best of 0, 12, 16 and 20 for all recipients and
+// for 8 of them. Measured, us per variant, all (8): FP32 24 slots forward 0 words
+// 0.56 (0.53), 12 0.55 (0.52), 16 0.54 (0.46), 20 0.64 (0.49); 28 slots backward 0
+// 0.61 (0.61), 12 0.55 (0.52), 16 0.56 (0.50), 20 0.68 (0.60); FP64 backward 24
+// slots 0 0.64 (0.50), 16 0.66 (0.52). FP64 backward of 16 slots loads its words
+// in two pairs of blocks (masked_scale_all): 0.39 (0.37) against 0.41 (0.37).
+__host__ __device__ constexpr int held_words(int prec, int nslot, int backward) {
+    if (prec == 0) {
+        if (nslot == 16) return backward ? 0 : 16;
+        if (nslot == 24 || nslot == 28) return backward ? 0 : 20;
+        return nslot <= 20 ? nslot : 16;
+    }
+    if (nslot <= 16) return nslot;
+    if (nslot == 20) return backward ? 12 : 16;
+    if (nslot == 24) return prec == 2 && backward ? 12 : 16;
+    if (nslot == 28) return 12;
+    return prec == 2 && !backward ? 16 : 20;
 }
 
 // Largest workgroup (in waves) a kernel with `nslot` slots may be launched

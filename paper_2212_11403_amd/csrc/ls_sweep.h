@@ -131,13 +131,6 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     // kappa, inside half's range, whatever the prior)
     constexpr bool SNORM = QH && PI && DIR == 1;
     static_assert(!QH || XMUL, "FP16-stored sweeps use the masked emission");
-    // FP32 single-wave groups that have a several-wave form (NP waves of SL
-    // slots, run_shape) add the column as it does: NP partial sums (of 20 and
-    // 28 slots: the last of its slots hold no donor and add 0). Not with
-    // FP16-stored vectors: their rounding after every update carries another
-    // order of the sum into the third digit.
-    constexpr bool kSplit = ONE && PT::id == 1 && !EVERY && !PI && split_slots(NSLOT) > 0;
-    constexpr int SL = kSplit ? split_slots(NSLOT) : NSLOT, NP = kSplit ? split_waves(NSLOT) : 1;
     __shared__ T red[2 * kRedStride];
 
     const int nwaves = uniform(blockDim.x >> 6);
@@ -216,21 +209,15 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     T S;                // sum of the resident vector
     T part_w = (T)0;    // SNORM: this lane's pi'-weighted partial sum
     T Wsum = (T)0;      // SNORM: the pi'-weighted column sum W'
-    // this lane's partial sums of the column
-    struct Part {
-        T x[NP];
-    };
     // the workgroup sum of a step's partials (with SNORM also W')
-    auto reduce = [&](const Part &part) __attribute__((always_inline)) -> T {
+    auto reduce = [&](T part) __attribute__((always_inline)) -> T {
         if constexpr (SNORM) {
-            T x[4] = {part.x[0], part_w, (T)0, (T)0};
+            T x[4] = {part, part_w, (T)0, (T)0};
             block_sum4<MAXW>(x, red, parity, wave);
             Wsum = x[1];
             return x[0];
-        } else if constexpr (kSplit) {
-            return waves_sum<NP>(part.x);
         } else {
-            return block_sum<MAXW>(part.x[0], red, parity, wave, nwaves);
+            return block_sum<MAXW>(part, red, parity, wave, nwaves);
         }
     };
 
@@ -266,29 +253,11 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     // Lane partial sums of the column: even slots into acc0, odd into acc1,
     // starting from slots 0 and 1 (the entries are never -0, so this equals
     // adding them to zero).
-    struct Acc {
-        T a[NP], b[NP];
-    };
-    auto accumulate = [&](int s, T x, Acc &acc) __attribute__((always_inline)) {
-        // (kSplit: a wave's regular slots come four at a time, then its special
-        // ones, as the words are handed out)
-        const int q = kSplit ? s / 4 % NP : 0;
-        T &acc0 = acc.a[q], &acc1 = acc.b[q];
-        if constexpr (kSplit) s = s / 4 / NP * 4 + s % 4;
+    auto accumulate = [&](int s, T x, T &acc0, T &acc1) __attribute__((always_inline)) {
         if (s == 0) acc0 = x;
         else if (s == 1) acc1 = x;
         else if (s & 1) acc1 += x;
         else acc0 += x;
-    };
-    auto acc_start = [&](Acc &acc) __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < NP; ++q) acc.b[q] = (T)0;
-    };
-    auto acc_parts = [&](const Acc &acc) __attribute__((always_inline)) -> Part {
-        Part p;
-#pragma unroll
-        for (int q = 0; q < NP; ++q) p.x[q] = acc.a[q] + acc.b[q];
-        return p;
     };
     // the column sum a step hands on: the backward with a prior matrix sums
     // pi' v (its normaliser W'), every other sweep v itself; the FP16-stored
@@ -301,14 +270,14 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         else if (s & 1) acc1 = fma(pv[s], x, acc1);
         else acc0 = fma(pv[s], x, acc0);
     };
-    auto account_sum = [&](int s, T x, Acc &acc) __attribute__((always_inline)) {
+    auto account_sum = [&](int s, T x, T &acc0, T &acc1) __attribute__((always_inline)) {
         if constexpr (SNORM) {
-            accumulate(s, x, acc);
+            accumulate(s, x, acc0, acc1);
             weighted(s, x, aw0, aw1);
         } else if constexpr (PI && DIR == 1) {
-            weighted(s, x, acc.a[0], acc.b[0]);
+            weighted(s, x, acc0, acc1);
         } else {
-            accumulate(s, x, acc);
+            accumulate(s, x, acc0, acc1);
         }
     };
     // FP16 storage: each new vector is rounded to half at every step, so the
@@ -334,12 +303,36 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
     // Narrow single-wave groups read the row words one variant ahead, beside
     // the coefficients (8 slots: 16 scalar registers; FP64, whose steps are
     // longer, also 12: in FP32 the copies cost more there than the wait, N = 640
-    // all recipients 0.46 us per variant against 0.42). In a group of several
+    // 0.46 us per variant against 0.32 with the words held, below). In a group of several
     // waves the wait for the exchange through LDS waits for scalar loads too,
     // so the loads gain nothing there and the copies cost 5 to 10%.
     constexpr bool AHEAD = ONE && NSLOT <= (sizeof(T) == 8 ? 12 : 8);
     struct Words {
         uint64_t w[AHEAD ? NSLOT : 1];
+    };
+    // The other single-wave groups load the first HELD row words together at the
+    // top of the step. Left to the scheduler, which puts registers first, each
+    // block of slots loads its own and waits for a round trip to memory of its
+    // own; all of them at once leave too few scalar registers from 24 slots up.
+    // us per variant, forward / backward, left to the scheduler -> held: FP32
+    // N = 640 0.44/0.47 -> 0.32/0.35, N = 1,450 0.56/0.53 -> 0.53/0.53 (8
+    // recipients 0.53/0.53 -> 0.46/0.50), N = 2,000 0.66/0.65 -> 0.62/0.58; FP16
+    // stored N = 1,000 0.51/0.50 -> 0.41/0.37, N = 1,600 0.74/0.90 -> 0.74/0.74.
+    constexpr int HELD = ONE && !AHEAD && XMUL ? held_words(PT::id, NSLOT, DIR) : 0;
+    struct Held {
+        uint64_t w[HELD > 0 ? HELD : 1];
+    };
+    auto hold_words = [&](int l) __attribute__((always_inline)) -> Held {
+        Held x;
+        if constexpr (HELD > 0) {
+            const uint64_t *row = Hr + (int64_t)l * a.hr_stride;
+#pragma unroll
+            for (int s = 0; s < HELD; ++s) x.w[s] = mask_of(row, s);
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            x.w[0] = 0;
+        }
+        return x;
     };
     auto words_at = [&](int l) __attribute__((always_inline)) -> Words {
         Words x;
@@ -382,15 +375,15 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         flip = uniform((int)(rb != on_match)) ? ~0ull : 0ull;
     };
     auto xmul_all = [&](auto mask, uint64_t flip, T r) __attribute__((always_inline)) {
-        masked_scale_all<NSLOT, ONE && !QH>(v, mask, flip, r);
+        masked_scale_all<NSLOT, ONE && HELD == 0 && !QH>(v, mask, flip, r);
     };
-    // v <- theta^l (.) (c v + b); returns this lane's partial sums
+    // v <- theta^l (.) (c v + b); returns this lane's partial sum
     auto step = [&](int l, uint64_t sw_bits, T em, T ex, T c, T b_s, const Words &wx)
-                    __attribute__((always_inline)) -> Part {
+                    __attribute__((always_inline)) -> T {
         const uint64_t *row = Hr + (int64_t)l * a.hr_stride;
+        const Held hx = hold_words(l);
         const T b = in_vgpr(b_s);
-        Acc acc;
-        acc_start(acc);
+        T acc0, acc1 = (T)0;
         if constexpr (XMUL) {
             T r;
             uint64_t flip;
@@ -412,13 +405,14 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             // FP16 storage rounds what a table holds: the backward vector
             // kappa beta^l before its emission, the forward kappa alpha^l
             if constexpr (DIR == 1) quantise();
-            xmul_all([&](int s) __attribute__((always_inline)) { return step_mask(row, wx, s); },
-                     flip, r);
+            xmul_all([&](int s) __attribute__((always_inline)) {
+                return s < HELD ? hx.w[s < HELD ? s : 0] : step_mask(row, wx, s);
+            }, flip, r);
             if constexpr (DIR == 0) quantise();
 #pragma unroll
-            for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc);
+            for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc0, acc1);
             if constexpr (SNORM) part_w = aw0 + aw1;
-            return acc_parts(acc);
+            return acc0 + acc1;
         }
         T ta, tb;
         thetas(sw_bits, em, ex, ta, tb);
@@ -430,9 +424,9 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             else bb = (s < NR) ? (s == 0 ? b * keep0 : b) : b * spec_keep[s - NR];
             const T nv = th * fma(c, (T)v[s], bb);
             v[s] = nv;
-            account_sum(s, nv, acc);
+            account_sum(s, nv, acc0, acc1);
         }
-        return acc_parts(acc);
+        return acc0 + acc1;
     };
     // v <- c v + b (no emission): the backward vector before theta^l
     auto affine = [&](T c, T b) __attribute__((always_inline)) {
@@ -440,16 +434,15 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         for (int s = 0; s < NSLOT; ++s) v[s] = keep_lanes(s, fma(c, v[s], b));
         quantise();
     };
-    // v <- theta^l (.) v; returns this lane's partial sums. The scalars of the
+    // v <- theta^l (.) v; returns this lane's partial sum. The scalars of the
     // variant are read here unless the caller has them (`ahead`).
     auto emit = [&](int l, uint64_t sw_bits, T em, T ex, const Words &wx, auto ahead)
-                    __attribute__((always_inline)) -> Part {
+                    __attribute__((always_inline)) -> T {
         constexpr bool HAVE = decltype(ahead)::value;
         const uint64_t *row = Hr + (int64_t)l * a.hr_stride;
         T ta, tb;
         if constexpr (!HAVE) emis_at(l, em, ex);
-        Acc acc;
-        acc_start(acc);
+        T acc0, acc1 = (T)0;
         if constexpr (XMUL) {
             T r;
             uint64_t flip;
@@ -459,9 +452,9 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 else return mask_of(row, s);
             }, flip, r);
 #pragma unroll
-            for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc);
+            for (int s = 0; s < NSLOT; ++s) account_sum(s, v[s], acc0, acc1);
             if constexpr (SNORM) part_w = aw0 + aw1;
-            return acc_parts(acc);
+            return acc0 + acc1;
         }
         thetas(HAVE ? sw_bits : row[self_off], em, ex, ta, tb);
 #pragma unroll
@@ -472,9 +465,9 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             const T th = lane_bit(word) ? tb : ta;
             const T nv = th * v[s];
             v[s] = nv;
-            account_sum(s, nv, acc);
+            account_sum(s, nv, acc0, acc1);
         }
-        return acc_parts(acc);
+        return acc0 + acc1;
     };
     // Narrow single-wave groups keep the element of a row that each lane and slot
     // writes at a target (one past every row for lanes without a donor, whose
@@ -683,11 +676,10 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
             l = 0;
         } else {
             l = a.l0 + 1;
-            Acc acc;  // same order as in step()
-            acc_start(acc);
+            T acc0, acc1 = (T)0;  // same order as in step()
 #pragma unroll
-            for (int s = 0; s < NSLOT; ++s) accumulate(s, v[s], acc);
-            S = reduce(acc_parts(acc));
+            for (int s = 0; s < NSLOT; ++s) accumulate(s, v[s], acc0, acc1);
+            S = reduce(acc0 + acc1);
         }
         // the coefficients and the recipient's own word are read one variant
         // ahead, so their latency overlaps the previous step, and c of the
@@ -742,7 +734,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 w_nx = self_word(ln);
                 x_nx = words_at(ln);
                 const T c = coef_c(A, S);
-                Part part = step(l, wb, em, ex, c, B, wx);
+                T part = step(l, wb, em, ex, c, B, wx);
                 buf_store((IO)c, rs_c, c_voff, (l - a.l0 - 1) * a.R * (int)sizeof(IO));
                 S = reduce(part);
                 account(S);
@@ -828,7 +820,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
                 // -> 18.0 ms per 2,048 variants with c formed after the
                 // reduction instead)
                 const T c = coef_c(A, S);
-                Part part = step(l, wb, em, ex, c, b, wx);
+                T part = step(l, wb, em, ex, c, b, wx);
                 S = reduce(part);
                 account(S);
             }
@@ -888,7 +880,7 @@ sweep_kernel(const uint64_t *__restrict__ Hr, const typename PT::T *__restrict__
         } else if (a.t < lstart) {
             // each column sum enters the log scale right after its
             // reduction (off the path to the next step's coefficients)
-            Part part = emit(lstart, 0, (T)0, (T)0, Words{}, std::false_type{});
+            T part = emit(lstart, 0, (T)0, (T)0, Words{}, std::false_type{});
             S = reduce(part);
             account(S);
             int l = lstart - 1;

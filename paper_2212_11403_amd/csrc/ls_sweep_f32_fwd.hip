@@ -31,8 +31,7 @@ static hipError_t launch_one(const SweepPtrs &p, const SweepArgs &a, int nwaves,
     return hipGetLastError();
 }
 
-hipError_t launch_sweep_f32_fwd(const SweepPtrs &p, const SweepArgs &a, Shape chosen, hipStream_t st) {
-    const Shape shape = run_shape(chosen, a.nblk);
+hipError_t launch_sweep_f32_fwd(const SweepPtrs &p, const SweepArgs &a, Shape shape, hipStream_t st) {
     switch (shape.nslot) {
 #define LS_CASE(n) \
     case n:        \

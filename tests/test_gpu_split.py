@@ -1,6 +1,6 @@
-"""Single waves that may run as several (FP32 arithmetic, 513 to 2,048
-haplotypes): a call over few recipients gives the bits of the call over all of
-them, whichever form each runs, through the C ABI (libls.so)."""
+"""Single waves of 513 to 2,048 haplotypes (row words held, of every slot count):
+a call over few recipients gives the bits of the call over all of them, through
+the C ABI (libls.so)."""
 
 from __future__ import annotations
 
@@ -24,7 +24,7 @@ def ls():
 
 
 # every slot count (12 to 32), its fewest and most words, full and ragged last
-# words, the recipients at which the form changes (512)
+# words, few recipients and more than the card's compute units
 @pytest.mark.parametrize("vec", [False, True])
 @pytest.mark.parametrize("N", [513, 575, 768, 769, 1024, 1025, 1088, 1280, 1281, 1536, 1537, 1601,
                                1792, 1793, 2047, 2048])
